@@ -104,7 +104,9 @@ typedef enum bitrev_path {
   BITREV_PATH_NONE = 0,  /* nothing to do (in place with n <= 2, or no rows) */
   BITREV_PATH_WAVE = 1,  /* n <= 64: one wavefront per array, lane shuffles */
   BITREV_PATH_TILE = 2,  /* tiles of 2^b x 2^b staged through LDS */
-  BITREV_PATH_BATCHED = 3 /* persistent batched kernel (tiles + whole-array LDS) */
+  BITREV_PATH_BATCHED = 3, /* persistent batched kernel (tiles + whole-array LDS) */
+  BITREV_PATH_ROWS = 4   /* two or more short rows: whole rows staged through LDS,
+                          * work_items chunks of rows (no configuration forced) */
 } bitrev_path_t;
 
 typedef struct bitrev_plan {

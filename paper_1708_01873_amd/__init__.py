@@ -26,7 +26,7 @@ ERROR_WORKSPACE = 3
 ERROR_HIP = 4
 ERROR_NOT_SUPPORTED = 5
 
-PATH_NONE, PATH_WAVE, PATH_TILE, PATH_BATCHED = 0, 1, 2, 3
+PATH_NONE, PATH_WAVE, PATH_TILE, PATH_BATCHED, PATH_ROWS = 0, 1, 2, 3, 4
 MODE_INPLACE, MODE_OUTOFPLACE, MODE_BATCHED = 0, 1, 2
 ORDER_DEFAULT, ORDER_NATURAL, ORDER_BALANCED, ORDER_GROUPED = 0, 1, 2, 3
 VARIANT_DEFAULT, VARIANT_ONE_ITEM, VARIANT_PIPELINED, VARIANT_REGISTER_STAGED = 0, 1, 2, 3

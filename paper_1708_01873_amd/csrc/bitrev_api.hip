@@ -256,6 +256,15 @@ void merge_rows(const std::vector<PlanRow>& rows, int kind, int s, int d, int bm
 }
 
 
+// Whether a tuning file's plan rows decide anything for this launch.
+bool user_rows_apply(int kind, int s, uint64_t footprint, const DeviceInfo& dev) {
+  PlanFields f;
+  std::lock_guard<std::mutex> lock(g_tune_mu);
+  if (g_user_rows.empty()) return false;
+  merge_rows(g_user_rows, kind, s, 0, 0, footprint_class(footprint), dev, &f);
+  return f.b || f.wg || f.order || f.variant || f.xcd || f.hints;
+}
+
 bitrev_status_t load_tuning_file(const char* path) {
   if (path == NULL) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -398,6 +407,11 @@ bool valid_config(const bitrev_config_t* c) {
          c->xcd_remap >= 0 && c->xcd_remap <= 2 && c->cache_hints >= 0 && c->cache_hints <= 4;
 }
 
+bool config_set(const bitrev_config_t* c) {
+  return c && (c->tile_bits || c->grid_blocks || c->order || c->variant || c->xcd_remap ||
+               c->cache_hints);
+}
+
 uint32_t round_up(uint64_t v, uint32_t to) {
   const uint64_t r = (v + to - 1) / to * to;
   return (uint32_t)(r > 0xFFFFFFFFull ? 0xFFFFFFFFull / to * to : r);
@@ -426,11 +440,73 @@ struct Plan {
   uint64_t items_per_seg = 0;
   uint64_t total = 0;
   size_t lds = 0;
+  int chunk_log2 = 0;      // whole-row path: bytes per workgroup
+  bool gather = false;
 };
 
-// Plan for a plain call (mode 0 or 1) on `rows` arrays of 2^k elements.
+// The whole-row path (bitrev_rows.hpp) for `rows` >= 2 arrays of 2^k elements
+// whose accesses stay 4-byte aligned: true and *p filled where it is taken,
+// given the tile plan *p.  The lines, each with both sides measured (kernel
+// time, three matrices in turn):
+//  - rows of at most 32 KiB; of 64 KiB only off the 16-byte grid, where the
+//    tile kernels move single elements (float32 2^14 at a pitch of n + 2,
+//    32 MiB: 15.6 -> 11.4 us; aligned complex64 2^13: 10.7 against 11.1);
+//  - where the tile plan has one tile per row (k = 2b), its accesses are
+//    linear too: it stays from 4 KiB rows (float32 2^10 8 MiB: 4.35 against
+//    4.56 us, complex128 2^10 128 MiB: 42.3 against 43.2) and, at 64 MiB
+//    and more, from 1 KiB rows of b >= 4 (float32 2^8: 64 MiB 20.9 -> 19.8,
+//    but 96 MiB 31.2 against 32.9; below 64 MiB 12.2 -> 10.5 at 32 MiB);
+//  - bytes beyond 8 KiB rows stay: the gather's lanes then share LDS banks
+//    (2^14: 12.0 against 21.1 us).
+// Write-through stores with streaming loads from 64 MiB (complex64 2^10 64
+// MiB 20.1 -> 19.6 us, 128 MiB 47.5 -> 42.4; at 32 MiB out of place 10.5
+// against 10.8) and for the gathers of 1- and 2-byte elements from 32 MiB
+// (int16 2^4 in place 12.2 -> 10.8); plain stores where rows end inside a
+// 64-byte line, which two workgroups then write (float64 2^9 at n + 2, 256
+// MiB: 95 against 107 us).
+bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool whole_lines,
+               uint64_t footprint, Plan* p) {
+  const uint64_t rb = (uint64_t)s << k;
+  const int c = s == 16 ? 0 : s == 8 ? 1 : s == 4 ? 2 : s == 2 ? 3 : 4;
+  if (rows < 2 || k > 16 || align < 4 || (rb < 16 && !contiguous)) return false;
+  const bool aligned = align == 16;
+  if (rb > (aligned ? 32768u : 65536u) || (s == 1 && k > 13)) return false;
+  const bool linear_tile = p->path == BITREV_PATH_TILE && p->m == 0 && p->vec && p->b >= 4;
+  if (linear_tile && (rb >= 4096 || (rb >= 1024 && footprint >= (64ull << 20)))) return false;
+  const bool gather = s == 1 || k < 2 * c;
+  int lb;
+  if (gather) {
+    lb = s > 1 ? 14 : rb > 4096 ? 13 : 12;
+  } else {
+    lb = s == 16 ? 13 : 14;
+    while ((1ull << lb) < rb) ++lb;
+  }
+  const uint64_t runs = rb < 16 ? (rows * rb) / 16 : rows;
+  const uint64_t per = rb < 16 ? (1u << lb) / 16 : (1ull << lb) / rb;
+  const uint64_t chunks = runs ? (runs + per - 1) / per : 1;
+  const int hints = (align == 16 && whole_lines &&
+                     footprint >= ((gather && s <= 2 ? 32ull : 64ull) << 20))
+                        ? kHintStreamWriteThrough
+                        : kHintPlain;
+  *p = Plan();
+  p->path = BITREV_PATH_ROWS;
+  p->order = 1;
+  p->xcd_remap = 2;
+  p->variant = 0;
+  p->threads = rows_block_threads(s, lb, gather);
+  p->total = chunks;
+  p->grid = (uint32_t)(chunks < (1u << 20) ? chunks : (1u << 20));
+  p->hints = hints;
+  p->lds = (size_t)1 << lb;
+  p->chunk_log2 = lb;
+  p->gather = gather;
+  return true;
+}
+
+// Plan for a plain call (mode 0 or 1) on `rows` arrays of 2^k elements by the
+// tile and wavefront kernels.
 // align: the largest power of two (<= 16) dividing both data pointers.
-bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, const bitrev_config_t* cfg,
+bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_config_t* cfg,
                            size_t align, const DeviceInfo& d, bool have_device, Plan* p) {
   *p = Plan();
   if (rows == 0 || (mode == kModeInplace && k <= 1)) return BITREV_SUCCESS;
@@ -502,6 +578,28 @@ bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, const bitrev_co
     p->grid = default_grid(p->total, d);
   }
   return BITREV_SUCCESS;
+}
+
+// Plan for a plain call: whole rows where that path is the better one and
+// neither the caller's configuration nor a tuning file decides.  The pitches
+// are in elements between consecutive arrays.
+bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, uint64_t src_pitch,
+                           uint64_t dst_pitch, const bitrev_config_t* cfg, size_t align,
+                           const DeviceInfo& d, bool have_device, Plan* p) {
+  const bitrev_status_t st = plan_tiles(mode, k, s, rows, cfg, align, d, have_device, p);
+  if (st != BITREV_SUCCESS || p->path == BITREV_PATH_NONE || rows < 2 || k > 16 ||
+      config_set(cfg))
+    return st;
+  const TuneEntry te = tune_lookup(mode, s, k);
+  if (te.tile_bits || te.wg_per_cu || te.order || te.variant || te.xcd_remap || te.cache_hints)
+    return st;
+  const uint64_t n = 1ull << k, footprint = (n * (uint64_t)s) * (uint64_t)rows;
+  if (user_rows_apply(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, footprint, d))
+    return st;
+  const bool contiguous = src_pitch == n && dst_pitch == n;
+  const bool whole_lines = contiguous || ((src_pitch * s) % 64 == 0 && (dst_pitch * s) % 64 == 0);
+  plan_rows(k, s, (uint64_t)rows, align, contiguous, whole_lines, footprint, p);
+  return st;
 }
 
 // Workgroups of the batched kernel that fit on one CU at once: limited by
@@ -609,6 +707,33 @@ hipError_t launch_wave(int s, const Plan& p, const void* src, void* dst, int k, 
   }
 }
 
+hipError_t launch_row_chunks(int s, const Plan& p, const void* src, void* dst, int k,
+                             int64_t rows, uint64_t src_stride, uint64_t dst_stride,
+                             hipStream_t st) {
+  const uint64_t rb = (uint64_t)s << k;
+  RowsLaunch a;
+  a.src = src;
+  a.dst = dst;
+  a.k = k;
+  if (rb < 16) {  // contiguous: one run of vectors, then what is left
+    a.runs = (uint64_t)rows * rb / 16;
+    a.run_log2 = 0;
+    a.tail = (uint32_t)((uint64_t)rows * rb % 16 / s);
+    a.src_pitch = a.dst_pitch = 16;
+  } else {
+    a.runs = (uint64_t)rows;
+    a.run_log2 = footprint_class(rb / 16);
+    a.tail = 0;
+    a.src_pitch = src_stride * s;
+    a.dst_pitch = dst_stride * s;
+  }
+  a.chunk_log2 = p.chunk_log2;
+  a.gather = p.gather;
+  a.hints = p.hints;
+  a.grid = p.grid;
+  return launch_rows(s, a, st);
+}
+
 size_t pointer_align(const void* a, const void* b) {
   const uintptr_t v = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b);
   size_t al = 16;
@@ -685,13 +810,16 @@ bitrev_status_t run_plain(const void* src, void* dst, int k, int64_t rows, size_
     if (sa < align) align = sa;
     if (da < align) align = da;
   }
-  st = plan_plain(inplace ? kModeInplace : kModeOutofplace, k, (int)s, rows, cfg, align, d, true,
-                  &p);
+  st = plan_plain(inplace ? kModeInplace : kModeOutofplace, k, (int)s, rows, src_stride,
+                  dst_stride, cfg, align, d, true, &p);
   if (st != BITREV_SUCCESS) return st;
   hipError_t e = hipSuccess;
-  if (p.path == BITREV_PATH_WAVE) {
+  if (p.path == BITREV_PATH_WAVE || p.path == BITREV_PATH_ROWS) {
     if (timed) e = hipEventRecord(static_cast<hipEvent_t>(ev_start), hs);
-    if (e == hipSuccess) e = launch_wave((int)s, p, src, dst, k, rows, src_stride, dst_stride, hs);
+    if (e == hipSuccess)
+      e = p.path == BITREV_PATH_ROWS
+              ? launch_row_chunks((int)s, p, src, dst, k, rows, src_stride, dst_stride, hs)
+              : launch_wave((int)s, p, src, dst, k, rows, src_stride, dst_stride, hs);
     if (timed && e == hipSuccess) e = hipEventRecord(static_cast<hipEvent_t>(ev_stop), hs);
   } else if (p.path == BITREV_PATH_TILE) {
     e = launch_tile(inplace, (int)s, p, src, dst, src_stride, dst_stride, d, hs,
@@ -1330,7 +1458,8 @@ bitrev_status_t bitrev_plan_query(int log2n, size_t elem_size, int64_t rows, int
   if (st != BITREV_SUCCESS) return st;
   Plan p;
   st = (mode == 2) ? plan_batched((int)elem_size, cfg, d, have_device, false, &p)
-                   : plan_plain(mode, log2n, (int)elem_size, rows, cfg, 16, d, have_device, &p);
+                   : plan_plain(mode, log2n, (int)elem_size, rows, 1ull << log2n, 1ull << log2n,
+                                cfg, 16, d, have_device, &p);
   if (st != BITREV_SUCCESS) return st;
   memset(plan, 0, sizeof *plan);
   plan->path = p.path;
@@ -1342,7 +1471,8 @@ bitrev_status_t bitrev_plan_query(int log2n, size_t elem_size, int64_t rows, int
   plan->vector_access = p.vec ? 1 : 0;
   plan->variant = p.path == BITREV_PATH_TILE ? p.variant : 0;
   plan->xcd_remap = (p.path == BITREV_PATH_TILE || p.path == BITREV_PATH_BATCHED) ? p.xcd_remap : 0;
-  plan->cache_hints = p.path == BITREV_PATH_TILE ? p.hints + 1 : 0;
+  plan->cache_hints =
+      (p.path == BITREV_PATH_TILE || p.path == BITREV_PATH_ROWS) ? p.hints + 1 : 0;
   plan->work_items = p.total;
   plan->lds_bytes = p.lds;
   return BITREV_SUCCESS;
@@ -1390,7 +1520,7 @@ bitrev_status_t bitrev_copy_tiled(const void* src, void* dst, int log2n, size_t 
   bitrev_status_t st = device_info(&d, false);
   if (st != BITREV_SUCCESS) return st;
   Plan p;
-  st = plan_plain(kModeOutofplace, log2n, (int)elem_size, 1, cfg, pointer_align(src, dst), d, true,
+  st = plan_tiles(kModeOutofplace, log2n, (int)elem_size, 1, cfg, pointer_align(src, dst), d, true,
                   &p);
   if (st != BITREV_SUCCESS) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);

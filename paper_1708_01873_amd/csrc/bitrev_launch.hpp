@@ -43,6 +43,24 @@ struct WaveLaunch {
   uint64_t dst_stride = 0;
 };
 
+// Whole rows in LDS (bitrev_rows.hpp): `runs` runs of 2^run_log2 16-byte
+// vectors, the rows or (run_log2 = 0) the vectors of contiguous rows shorter
+// than one, then `tail` elements.
+struct RowsLaunch {
+  const void* src;
+  void* dst;
+  int k;
+  uint64_t runs;
+  int run_log2;
+  uint32_t tail;
+  uint64_t src_pitch;       // bytes between consecutive runs
+  uint64_t dst_pitch;
+  int chunk_log2;           // bytes per workgroup
+  bool gather;              // element by element (k < 2 log2(16 / s), and bytes)
+  int hints;                // plain or streaming loads with write-through stores
+  uint32_t grid;
+};
+
 struct DitLaunch {
   TileLaunch t;             // the tile geometry (src == dst: in place)
   int stages;               // DIT levels fused after the reversal, <= b
@@ -113,6 +131,10 @@ BITREV_DECLARE_LAUNCHERS(16)
 
 hipError_t launch_dit_s8(int b, bool vec, const DitLaunch& a, hipStream_t st);
 hipError_t launch_dit_s16(int b, bool vec, const DitLaunch& a, hipStream_t st);
+
+// Threads per workgroup of the whole-row kernels.
+int rows_block_threads(int s, int chunk_log2, bool gather);
+hipError_t launch_rows(int s, const RowsLaunch& a, hipStream_t st);
 
 hipError_t launch_batched_prep(const BatchedLaunch& a, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, uint32_t grid, int hints,

@@ -1,0 +1,187 @@
+// Whole rows in LDS: the bit reversal of many short arrays of equal length.
+// A workgroup takes a run of whole rows, so both its reads and its writes are
+// linear in memory whatever the row length, and nothing is shared between
+// workgroups: in place, every row is read before the barrier and written
+// after it.
+//
+// Bound by memory: one 16-byte LDS write and one read per 16 bytes moved is
+// far below the LDS rate.  The tile kernels split a short row into 2^b x 2^b
+// tiles of 2^b s bytes a row (k = 5, complex64: 32 bytes; 9, float32: 64), and
+// the wavefront kernel for k <= 6 leaves 64 - 2^k lanes idle.  Measured,
+// kernel time at 32 MiB, three arrays in turn (a copy of the bytes: 10.5 us):
+// complex64 k = 2 67.7 -> 10.5 us, 5 16.5 -> 10.5, 7 15.9 -> 10.6, 11 11.3 ->
+// 10.8; float32 3 59.1 -> 10.1, 9 20.9 -> 10.9; int16 9 21.2 -> 10.7; uint8 7
+// 107 -> 13; rows at a pitch of n + 2: float64 9 31.9 -> 11.0, float32 13
+// 17.5 -> 11.5.  Below 4 MiB both are launch-bound and equal.
+#pragma once
+
+#include "bitrev_device.hpp"
+
+namespace bitrev {
+
+// 16 bytes at any multiple of 4 bytes: gfx950's wide global accesses need
+// dword alignment only, so rows at a padded pitch move as vectors too.
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+// log2 of the elements per 16-byte vector.
+__host__ __device__ constexpr int vec_log2(int s) { return s == 16 ? 0 : s == 8 ? 1 : s == 4 ? 2 : s == 2 ? 3 : 4; }
+
+// Transposed groups of CE = 16 / s vectors a thread moves per chunk of 2^lb
+// bytes.  One group (two 16-byte accesses for complex64) ran 1-4% ahead of
+// two from 64 MiB up and level below; wider chunks need more to stay within
+// 1024 threads, and at 16 bytes 8 KiB chunks of one were 2% ahead of 16 KiB
+// of two at 128-512 MiB.
+__host__ __device__ constexpr int rows_groups(int s, int lb) {
+  return s == 16 ? (lb >= 16 ? 4 : lb >= 14 ? 2 : 1) : (s == 8 && lb >= 15) ? 2 : 1;
+}
+
+// Threads of a workgroup of k_rows whose chunk has 2^lb bytes.
+__host__ __device__ constexpr int rows_threads(int s, int lb) {
+  return (1 << (lb - 4)) / (rows_groups(s, lb) * (16 / s));
+}
+
+// Threads of a workgroup of k_rows_gather: four vectors each.
+__host__ __device__ constexpr int gather_threads(int lb) { return 1 << (lb - 6); }
+
+// Physical slot of 16-byte slot v: the low three bits (the eight slots of a
+// 128-byte LDS line) XORed with the fold of all higher bits in groups of
+// three.  The scatter's eight neighbouring lanes differ in three consecutive
+// slot bits, which the fold maps onto the three low ones, and the linear
+// reads stay permutations within aligned runs of eight.
+__device__ __forceinline__ uint32_t rows_slot(uint32_t v) {
+  return v ^ (((v >> 3) ^ (v >> 6) ^ (v >> 9)) & 7u);
+}
+
+// The CE vectors a[e] of CE elements, as CE vectors r[j] with
+// r[j][rev(e)] = a[e][j] (e and j of vec_log2(S) bits).
+template <int S> __device__ __forceinline__ void rows_transpose(const u32x4 (&a)[16 / S], u32x4 (&r)[16 / S]) {
+  if constexpr (S == 16) {
+    r[0] = a[0];
+  } else if constexpr (S == 8) {
+    r[0] = __builtin_shufflevector(a[0], a[1], 0, 1, 4, 5);
+    r[1] = __builtin_shufflevector(a[0], a[1], 2, 3, 6, 7);
+  } else if constexpr (S == 4) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = u32x4{a[0][j], a[2][j], a[1][j], a[3][j]};
+  } else {
+    static_assert(S == 2, "2-byte elements");
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int d = 0; d < 4; ++d)  // halves 2d and 2d + 1 of r[j]
+        r[j][d] = __builtin_amdgcn_perm(a[crev(2 * d + 1, 3)][j >> 1], a[crev(2 * d, 3)][j >> 1],
+                                        (j & 1) ? 0x07060302u : 0x05040100u);
+  }
+}
+
+// Rows of 2^k elements, k >= 2 c (c = vec_log2(S)), 2^k S <= 2^LB bytes: a
+// thread loads the CE vectors at one offset q of the CE equal parts of a row
+// (part e holds the elements whose top c index bits are e), and their
+// transpose in registers is CE whole output vectors: element (e, q, j) of the
+// index [e | q | j] goes to [rev(j) | rev(q) | rev(e)], so output vector j is
+// vector [rev(j) | rev(q)] of the row.  One 16-byte LDS write and read per
+// vector turn the scattered vectors into linear runs.
+template <int S, int LB, int H>
+__global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, void* dst, int k,
+                                                             uint64_t rows, uint64_t src_pitch,
+                                                             uint64_t dst_pitch) {
+  constexpr int C = vec_log2(S), CE = 1 << C;
+  constexpr int NT = rows_threads(S, LB), T = rows_groups(S, LB), PT = T * CE;
+  constexpr uint32_t CHV = 1u << (LB - 4);  // vectors per chunk
+  __shared__ u32x4 lds[CHV];
+  const int w = k - 2 * C, lv = k - C;
+  const uint32_t wmask = (1u << w) - 1u, vmask = (1u << lv) - 1u;
+  const uint64_t step = (uint64_t)gridDim.x * (CHV >> lv);
+  for (uint64_t row0 = (uint64_t)blockIdx.x * (CHV >> lv); row0 < rows; row0 += step) {
+    const uint32_t live = rows - row0 < (CHV >> lv) ? (uint32_t)(rows - row0) : CHV >> lv;
+    const char* in = static_cast<const char*>(src) + row0 * src_pitch;
+    char* out = static_cast<char*>(dst) + row0 * dst_pitch;
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const uint32_t u = threadIdx.x + i * NT;
+      const uint32_t q = u & wmask, r = u >> w;
+      if (r < live) {
+        u32x4 a[CE], t[CE];
+        const char* p = in + r * src_pitch + q * 16u;
+#pragma unroll
+        for (int e = 0; e < CE; ++e)
+          a[e] = ld_hint<H>(reinterpret_cast<const u32x4_a4*>(p + ((size_t)e << (w + 4))));
+        rows_transpose<S>(a, t);
+        const uint32_t o = (r << lv) + rev_bits(q, w);
+#pragma unroll
+        for (int j = 0; j < CE; ++j) lds[rows_slot(o + ((uint32_t)crev(j, C) << w))] = t[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const uint32_t v = threadIdx.x + i * NT;
+      const uint32_t r = v >> lv;
+      if (r < live)
+        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + r * dst_pitch + (v & vmask) * 16u),
+                   (u32x4_a4)lds[rows_slot(v)]);
+    }
+    __syncthreads();
+  }
+}
+
+// Rows shorter than k = 2 c, and all rows of bytes: a chunk of rows goes to
+// LDS as it is, and each output vector gathers its elements one by one (bytes
+// need sixteen vectors for a transpose in registers; the gather holds one, and
+// its lanes read neighbouring bytes up to k = 12).  The data are `nrun` runs of
+// 2^lr vectors, `pitch` bytes apart: the rows, or single vectors (lr = 0,
+// pitch 16) of contiguous rows shorter than a vector; the `tail` elements
+// after the last whole run move alone.
+template <int S, int LB, int H>
+__global__ __launch_bounds__(gather_threads(LB)) void k_rows_gather(
+    const void* src, void* dst, int k, uint64_t nrun, int lr, uint32_t tail, uint64_t src_pitch,
+    uint64_t dst_pitch) {
+  typedef typename Bytes<S>::T E;
+  constexpr int CE = 16 / S, NT = gather_threads(LB), PT = 4;
+  constexpr uint32_t CHV = 1u << (LB - 4);
+  __shared__ u32x4 lds[CHV];
+  const E* le = reinterpret_cast<const E*>(lds);
+  const uint32_t nmask = (1u << k) - 1u, rmask = (1u << lr) - 1u;
+  const uint64_t step = (uint64_t)gridDim.x * (CHV >> lr);
+  for (uint64_t run0 = (uint64_t)blockIdx.x * (CHV >> lr); run0 < nrun; run0 += step) {
+    const uint32_t live = nrun - run0 < (CHV >> lr) ? (uint32_t)(nrun - run0) : CHV >> lr;
+    const char* in = static_cast<const char*>(src) + run0 * src_pitch;
+    char* out = static_cast<char*>(dst) + run0 * dst_pitch;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const uint32_t v = threadIdx.x + i * NT;
+      const uint32_t r = v >> lr;
+      if (r < live)
+        lds[v] = ld_hint<H>(
+            reinterpret_cast<const u32x4_a4*>(in + r * src_pitch + (v & rmask) * 16u));
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < PT; ++i) {
+      const uint32_t v = threadIdx.x + i * NT;
+      const uint32_t r = v >> lr;
+      if (r < live) {
+        Chunk<S, 16> c;
+#pragma unroll
+        for (int e = 0; e < CE; ++e) {
+          const uint32_t o = v * CE + e;
+          c.e[e] = le[(o & ~nmask) | rev_bits(o & nmask, k)];
+        }
+        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + r * dst_pitch + (v & rmask) * 16u),
+                   (u32x4_a4)c.v);
+      }
+    }
+    __syncthreads();
+  }
+  if (tail && blockIdx.x == 0 && threadIdx.x < 64) {  // less than a vector: one wavefront, in lanes
+    const E* in = reinterpret_cast<const E*>(static_cast<const char*>(src) + nrun * src_pitch);
+    E* out = reinterpret_cast<E*>(static_cast<char*>(dst) + nrun * dst_pitch);
+    const uint32_t o = threadIdx.x;
+    const uint32_t from = (o & ~nmask) | rev_bits(o & nmask, k);
+    E x = (E)0u;
+    if (o < tail) x = in[from];
+    if (o < tail) out[o] = x;
+  }
+}
+
+}  // namespace bitrev

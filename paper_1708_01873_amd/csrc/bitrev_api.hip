@@ -440,6 +440,7 @@ struct Plan {
   uint64_t items_per_seg = 0;
   uint64_t total = 0;
   size_t lds = 0;
+  bool persistent = false; // batched: the caller or a tuning file set the grid
   int chunk_log2 = 0;      // whole-row path: bytes per workgroup
   bool gather = false;
 };
@@ -641,6 +642,8 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
                                          : (te.xcd_remap ? te.xcd_remap : (tp.xcd ? tp.xcd : 1));
+  p->persistent =
+      (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || user_rows_apply(kind, s, 0, d);
   p->threads = threads_of(s, b, true);
   p->lds = tile_lds_bytes_for(s, b, 2);
   int per_cu = te.wg_per_cu > 0 ? te.wg_per_cu : tp.wg;
@@ -1337,11 +1340,30 @@ static bitrev_status_t run_batched(const void* src, void* data, int64_t data_ele
   a.data_elems = data_elems;
   a.ws = static_cast<int64_t*>(workspace);
   a.b = p.b;
+  // Arrays that move whole through LDS: those too short for a tile, and in
+  // batches of short arrays (under 16 KiB on average, no width forced) all up
+  // to 32 KiB (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500
+  // complex128 arrays of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
+  a.whole = 2 * p.b - 1;
+  const bool shorts = (uint64_t)data_elems / (uint64_t)num_arrays < 16384 / elem_size;
+  if (shorts && !(cfg && cfg->tile_bits))
+    while ((elem_size << (a.whole + 1)) <= 32768) ++a.whole;
+  a.hints = (uint64_t)data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
   a.balanced = order_code(p.order);
-  a.xcds = p.xcd_remap == 2 ? 1 : d.xcds;
+  // one item per workgroup runs in dispatch order: contiguous XCD ranges walk
+  // eight distant regions at once (4096 complex64 arrays: +10%)
+  const bool ranges = p.xcd_remap != 2 && (p.persistent || (cfg && cfg->xcd_remap));
+  a.xcds = ranges ? d.xcds : 1;
   a.grid = p.grid;
+  if (!p.persistent) {
+    // no more workgroups than the data hold tiles: those without an item
+    // cost 1 us per thousand (in short batches few arrays have tiles)
+    uint64_t most = ((uint64_t)data_elems >> (2 * p.b)) + 1;
+    if (shorts) most = most / 2 > 2u * (uint32_t)d.cus ? most / 2 : 2u * (uint32_t)d.cus;
+    if (most < a.grid) a.grid = round_up(most, (uint32_t)d.xcds);
+  }
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_batched_prep(a, hs);
+  hipError_t e = launch_batched_front((int)elem_size, a, hs);
   if (e != hipSuccess) return hip_fail(e);
   switch (elem_size) {
     case 1: e = launch_batched_s1(a, hs); break;
@@ -1428,7 +1450,7 @@ bitrev_status_t bitrev_batched_noalloc(void* data, int64_t data_elems, const int
   void* ws = nullptr;
   const bitrev_status_t st = scratch_address(&ws);
   if (st != BITREV_SUCCESS) return st;
-  // the prep kernel writes every workspace word the persistent kernel reads
+  // the first kernel writes every workspace word the persistent kernel reads
   // (header and scan), so the previous call's contents need no clearing
   return run_batched(NULL, data, data_elems, offsets, log2n, num_arrays, elem_size, ws,
                      sizeof(scratch), NULL, stream);

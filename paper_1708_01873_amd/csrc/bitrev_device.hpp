@@ -1175,23 +1175,6 @@ __device__ __forceinline__ void tile_pair_transpose(typename Bytes<S>::T* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Whole array in one workgroup's LDS (any 2^k that fits): load, barrier,
-// out[i] = lds[rev_k(i)].  One element per access; the padding of one
-// element every 32 breaks the power-of-two strides of the gather.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t small_slot(uint32_t i) { return i + (i >> 5); }
-
-template <int S, int NT>
-__device__ __forceinline__ void small_array(const typename Bytes<S>::T* src,
-                                            typename Bytes<S>::T* dst, int k,
-                                            typename Bytes<S>::T* lds) {
-  const uint32_t n = 1u << k;
-  for (uint32_t i = threadIdx.x; i < n; i += NT) lds[small_slot(i)] = src[i];
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < n; i += NT) dst[i] = lds[small_slot(rev_bits(i, k))];
-}
-
-// ---------------------------------------------------------------------------
 // Whole array in one wavefront (n = 2^k <= 64): lane i holds element i and
 // fetches element rev_k(i) from its lane with ds_bpermute, one dword at a
 // time.  No LDS storage and no barrier.

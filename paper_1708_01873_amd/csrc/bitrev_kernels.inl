@@ -733,10 +733,10 @@ __device__ __forceinline__ int64_t find_array(const int64_t* scan, int64_t num, 
   return lo;
 }
 
-// Batched, in place, persistent: the prep kernel has written the exclusive
-// scan of per-array work counts to ws[2..]; every workgroup walks the global
-// work ids with a grid stride, finds its array and runs either the
-// whole-array LDS routine (2^k < 2^(2b)) or one tile pair at width b.
+// Batched, in place, persistent: k_batched_front has permuted the arrays that
+// fit its LDS and written the exclusive scan of the tile pairs of the others
+// to ws[2..]; every workgroup walks the global work ids with a grid stride,
+// finds its array and swaps one tile pair at width b.
 template <int S, int B>
 __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched(
     void* data, const int64_t* offsets, const int32_t* log2n, int64_t num, const int64_t* ws,
@@ -748,57 +748,46 @@ __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched(
   const uint64_t total = (uint64_t)scan[num];
   for (uint64_t item = xcd_block(xcds); item < total; item += gridDim.x) {
     const int64_t a = find_array(scan, num, item);
-    const int k = log2n[a];
     E* base = static_cast<E*>(data) + offsets[a];
-    if (k < 2 * B) {
-      small_array<S, NT>(base, base, k, lds);
+    const int m = log2n[a] - 2 * B;
+    const uint32_t y = inplace_pair_at(m, item - (uint64_t)scan[a], balanced);
+    // an array after ones shorter than 16 bytes may start off the 16-byte
+    // grid: it moves element by element between HBM and LDS, which keeps
+    // this rare path from raising the kernel's register count (74 -> 56
+    // VGPRs for complex64 at b = 6: two workgroups per CU instead of one)
+    if ((reinterpret_cast<uintptr_t>(base) & 15u) == 0) {
+      // streaming loads, write-through stores: 4096 complex64 arrays of
+      // 2^8-2^20 elements 2.017 -> 1.947 ms (streaming stores: no gain)
+      tile_pair_inplace<S, B, true, NT, kHintStreamWriteThrough, false>(base, m, y, lds);
     } else {
-      const int m = k - 2 * B;
-      const uint32_t y = inplace_pair_at(m, item - (uint64_t)scan[a], balanced);
-      // an array after ones shorter than 16 bytes may start off the 16-byte
-      // grid: it moves element by element between HBM and LDS, which keeps
-      // this rare path from raising the kernel's register count (74 -> 56
-      // VGPRs for complex64 at b = 6: two workgroups per CU instead of one)
-      if ((reinterpret_cast<uintptr_t>(base) & 15u) == 0) {
-        // streaming loads, write-through stores: 4096 complex64 arrays of
-        // 2^8-2^20 elements 2.017 -> 1.947 ms (streaming stores: no gain)
-        tile_pair_inplace<S, B, true, NT, kHintStreamWriteThrough, false>(base, m, y, lds);
-      } else {
-        tile_pair_inplace_elem<S, B, NT, 1>(base, m, y, lds);
-      }
+      tile_pair_inplace_elem<S, B, NT, 1>(base, m, y, lds);
     }
     __syncthreads();
   }
 }
 
 // Batched, out of place: the same persistent walk, with one work item per
-// source tile (2^m per array) or per small array; dst holds the same layout.
+// source tile (2^m per array); dst holds the same layout.
 template <int S, int B>
 __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched_oop(
     const void* src, void* dst, const int64_t* offsets, const int32_t* log2n, int64_t num,
     const int64_t* ws, int balanced, int xcds) {
   typedef typename Bytes<S>::T E;
   constexpr int NT = tile_threads<S, B, true>();
-  __shared__ E lds[2 * TileShape<S, B, true>::TILE_E];
+  __shared__ E lds[TileShape<S, B, true>::TILE_E];
   const int64_t* scan = ws + 2;
   const uint64_t total = (uint64_t)scan[num];
   for (uint64_t item = xcd_block(xcds); item < total; item += gridDim.x) {
     const int64_t a = find_array(scan, num, item);
-    const int k = log2n[a];
     const E* in = static_cast<const E*>(src) + offsets[a];
     E* out = static_cast<E*>(dst) + offsets[a];
-    if (k < 2 * B) {
-      small_array<S, NT>(in, out, k, lds);
-    } else {
-      const int m = k - 2 * B;
-      const uint32_t local = (uint32_t)(item - (uint64_t)scan[a]);
-      const uint32_t y = oop_tile_at(m, local, balanced);
-      if (((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0) {
-        // plain accesses: write-through stores measured 1.8% slower here
-        tile_outofplace<S, B, true, NT>(in, out, m, y, lds);
-      } else {  // element by element, as in k_batched
-        tile_outofplace_elem<S, B, NT, 1>(in, out, m, y, lds);
-      }
+    const int m = log2n[a] - 2 * B;
+    const uint32_t y = oop_tile_at(m, (uint32_t)(item - (uint64_t)scan[a]), balanced);
+    if (((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0) {
+      // plain accesses: write-through stores measured 1.8% slower here
+      tile_outofplace<S, B, true, NT>(in, out, m, y, lds);
+    } else {  // element by element, as in k_batched
+      tile_outofplace_elem<S, B, NT, 1>(in, out, m, y, lds);
     }
     __syncthreads();
   }

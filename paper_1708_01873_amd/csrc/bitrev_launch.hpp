@@ -88,6 +88,8 @@ struct BatchedLaunch {
   int64_t data_elems;
   int64_t* ws;              // [0] invalid count, [1] first invalid, [2..] scan
   int b;
+  int whole;                // arrays of at most 2^whole elements move whole
+  int hints;                // CacheHint of those
   int balanced;
   int xcds;
   uint32_t grid;
@@ -136,7 +138,8 @@ hipError_t launch_dit_s16(int b, bool vec, const DitLaunch& a, hipStream_t st);
 int rows_block_threads(int s, int chunk_log2, bool gather);
 hipError_t launch_rows(int s, const RowsLaunch& a, hipStream_t st);
 
-hipError_t launch_batched_prep(const BatchedLaunch& a, hipStream_t st);
+// Scan of the tile work and the arrays that move whole (bitrev_batched.hip).
+hipError_t launch_batched_front(int s, const BatchedLaunch& a, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, uint32_t grid, int hints,
                        hipStream_t st);
 

@@ -1,6 +1,6 @@
 """HIP-graph capture of the batched permutation.
 
-``BatchedGraph`` records ``bitrev_batched`` (prep kernel + persistent kernel)
+``BatchedGraph`` records ``bitrev_batched`` (its two kernels)
 into a graph once and replays it with one launch.  The library allocates and
 synchronises nothing on this path and records no memset, so the capture holds
 exactly the two kernels.  Choose the configuration (e.g. with ``tune``)

@@ -168,10 +168,24 @@ def _config(tile_bits=0, grid_blocks=0, order=0, config=None, variant=0, xcd_rem
     return None
 
 
+_raw_stream = _current_device = None
+
+
+def _current_stream() -> int:
+    """The handle of torch's current stream (``current_stream().cuda_stream``
+    without building a Stream object: 0.3 instead of 2.7 us of a call)."""
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        import torch
+        _current_device = torch.cuda.current_device
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(_current_device())
+
+
 def _stream(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

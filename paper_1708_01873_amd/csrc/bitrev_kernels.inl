@@ -633,10 +633,11 @@ hipError_t dispatch_dit(int b, bool vec, const DitLaunch& a, hipStream_t st) {
 }
 #endif
 
-// Digit reversal (radix-2^D digits), in place (src == dst: pairs
-// y <= drev(y)) or out of place; the tile width B and the middle width m are
-// whole numbers of digits, so drev([x | y | z]) = [drev(z) | drev(y) | drev(x)].
-template <int S, int B, int D, bool VEC, int H>
+// Digit reversal (radix-2^D digits), in place (pairs y <= drev(y)) or out of
+// place; the tile width B and the middle width m are whole numbers of digits,
+// so drev([x | y | z]) = [drev(z) | drev(y) | drev(x)].  Out of place a
+// workgroup stages one tile: half the LDS of a pair.
+template <int S, int B, int D, bool VEC, int H, bool INPLACE>
 __global__ __launch_bounds__((tile_threads<S, B, VEC>())) void k_tile_digit(
     const void* src, void* dst, int m, uint64_t total_items, int order, int xcds) {
   static_assert(B % D == 0, "the tile width must be a whole number of digits");
@@ -644,25 +645,30 @@ __global__ __launch_bounds__((tile_threads<S, B, VEC>())) void k_tile_digit(
   typedef TileShape<S, B, VEC> Sh;
   constexpr int NT = tile_threads<S, B, VEC>();
   constexpr int PT = (Sh::CPT + NT - 1) / NT;
-  __shared__ E lds[2 * Sh::TILE_E];
-  const bool inplace = (src == dst);
+  __shared__ E lds[(INPLACE ? 2 : 1) * Sh::TILE_E];
   const uint64_t rowstride = 1ull << (m + B);
   const E* in = static_cast<const E*>(src);
   E* out = static_cast<E*>(dst);
   for (uint64_t item = xcd_block(xcds); item < total_items; item += gridDim.x) {
-    Chunk<S, Sh::VB> ra[PT], rb[PT];
+    Chunk<S, Sh::VB> ra[PT];
     // out of place any order of the source tiles works (each lands on its
     // own destination tile); the order code as for the bit-reversal kernels
-    const uint32_t y = inplace ? dinplace_pair_at(m, item, D) : oop_tile_at(m, (uint32_t)item, order);
+    const uint32_t y = INPLACE ? dinplace_pair_at(m, item, D) : oop_tile_at(m, (uint32_t)item, order);
     const uint32_t yr = drev_bits(y, m, D);
-    const bool two = inplace && (y != yr);
     tile_load<S, B, VEC, NT, PT, H>(ra, in, rowstride, y);
-    if (two) tile_load<S, B, VEC, NT, PT, H>(rb, in, rowstride, yr);
-    tile_scatter<S, B, VEC, NT, PT, D>(ra, lds);
-    if (two) tile_scatter<S, B, VEC, NT, PT, D>(rb, lds + Sh::TILE_E);
-    __syncthreads();
-    // tile y first, then its partner, as in the bit-reversal kernels
-    if (two) tile_store<S, B, VEC, NT, PT, H>(out, rowstride, y, lds + Sh::TILE_E);
+    if constexpr (INPLACE) {
+      Chunk<S, Sh::VB> rb[PT];
+      const bool two = y != yr;
+      if (two) tile_load<S, B, VEC, NT, PT, H>(rb, in, rowstride, yr);
+      tile_scatter<S, B, VEC, NT, PT, D>(ra, lds);
+      if (two) tile_scatter<S, B, VEC, NT, PT, D>(rb, lds + Sh::TILE_E);
+      __syncthreads();
+      // tile y first, then its partner, as in the bit-reversal kernels
+      if (two) tile_store<S, B, VEC, NT, PT, H>(out, rowstride, y, lds + Sh::TILE_E);
+    } else {
+      tile_scatter<S, B, VEC, NT, PT, D>(ra, lds);
+      __syncthreads();
+    }
     tile_store<S, B, VEC, NT, PT, H>(out, rowstride, yr, lds);
     __syncthreads();
   }
@@ -901,38 +907,33 @@ hipError_t dispatch_transpose(int b, bool vec, const TransposeLaunch& a, hipStre
   }
 }
 
+template <int S, int B, int D, bool VEC, int H>
+hipError_t run_digit_h(const TileLaunch& a, hipStream_t st) {
+  if (a.src == a.dst) {
+    hipLaunchKernelGGL((k_tile_digit<S, B, D, VEC, H, true>), dim3(a.grid),
+                       dim3(tile_threads<S, B, VEC>()), 0, st, a.src, a.dst, a.m, a.total_items,
+                       a.balanced, a.xcds);
+  } else {
+    hipLaunchKernelGGL((k_tile_digit<S, B, D, VEC, H, false>), dim3(a.grid),
+                       dim3(tile_threads<S, B, VEC>()), 0, st, a.src, a.dst, a.m, a.total_items,
+                       a.balanced, a.xcds);
+  }
+  return hipGetLastError();
+}
+
 template <int S, int D, int B = D>
 hipError_t dispatch_digit(int b, bool vec, const TileLaunch& a, hipStream_t st) {
   if constexpr (B > max_tile_bits(S)) {
     return hipErrorInvalidValue;
   } else {
-    if (b == B) {
-      if (vec) {
-        if (a.hints == kHintStreamLoads) {
-          hipLaunchKernelGGL((k_tile_digit<S, B, D, true, kHintStreamLoads>), dim3(a.grid),
-                             dim3(tile_threads<S, B, true>()), 0, st, a.src, a.dst, a.m,
-                             a.total_items, a.balanced, a.xcds);
-        } else if (a.hints == kHintStreamStores) {
-          hipLaunchKernelGGL((k_tile_digit<S, B, D, true, kHintStreamStores>), dim3(a.grid),
-                             dim3(tile_threads<S, B, true>()), 0, st, a.src, a.dst, a.m,
-                             a.total_items, a.balanced, a.xcds);
-        } else if (a.hints == kHintStreamWriteThrough) {
-          hipLaunchKernelGGL((k_tile_digit<S, B, D, true, kHintStreamWriteThrough>), dim3(a.grid),
-                             dim3(tile_threads<S, B, true>()), 0, st, a.src, a.dst, a.m,
-                             a.total_items, a.balanced, a.xcds);
-        } else {
-          hipLaunchKernelGGL((k_tile_digit<S, B, D, true, kHintPlain>), dim3(a.grid),
-                             dim3(tile_threads<S, B, true>()), 0, st, a.src, a.dst, a.m,
-                             a.total_items, a.balanced, a.xcds);
-        }
-      } else {
-        hipLaunchKernelGGL((k_tile_digit<S, B, D, false, kHintPlain>), dim3(a.grid),
-                           dim3(tile_threads<S, B, false>()), 0, st, a.src, a.dst, a.m,
-                           a.total_items, a.balanced, a.xcds);
-      }
-      return hipGetLastError();
+    if (b != B) return dispatch_digit<S, D, B + D>(b, vec, a, st);
+    if (!vec) return run_digit_h<S, B, D, false, kHintPlain>(a, st);
+    switch (a.hints) {
+      case kHintStreamLoads: return run_digit_h<S, B, D, true, kHintStreamLoads>(a, st);
+      case kHintStreamStores: return run_digit_h<S, B, D, true, kHintStreamStores>(a, st);
+      case kHintStreamWriteThrough: return run_digit_h<S, B, D, true, kHintStreamWriteThrough>(a, st);
+      default: return run_digit_h<S, B, D, true, kHintPlain>(a, st);
     }
-    return dispatch_digit<S, D, B + D>(b, vec, a, st);
   }
 }
 

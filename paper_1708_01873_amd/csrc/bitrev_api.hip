@@ -338,16 +338,67 @@ TuneEntry tune_lookup(int mode, int s, int k) {
 
 // The table's plan for a launch of `kind` covering `footprint` bytes; bm is
 // the tile width in use (0 while it is being chosen), d the digit width.
-// Fields no row sets stay 0.
-PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const DeviceInfo& dev) {
+// Fields no row sets stay 0.  `f` starts with what is already decided.
+PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const DeviceInfo& dev,
+                      PlanFields f = PlanFields()) {
   load_env_tuning();
   const int c = footprint_class(footprint);
-  PlanFields f;
   const std::vector<PlanRow>& builtin = builtin_rows();
   std::lock_guard<std::mutex> lock(g_tune_mu);
   for (int k = kind; k >= 0; k = kKindParent[k]) {
     merge_rows(g_user_rows, k, s, d, bm, c, dev, &f);
     merge_rows(builtin, k, s, d, bm, c, dev, &f);
+  }
+  return f;
+}
+
+// What the bytes and rows of an out-of-place launch on MI355X decide before
+// the table, whose rows know only powers of two and were measured on single
+// arrays (its choices stay wherever nothing is set here).  Kernel us, three
+// states in turn, before -> now.
+//  - Several rows, in dispatch order, which walks the rows one after the
+//    other where contiguous XCD ranges keep eight distant rows in flight:
+//    complex128 rows of 1 to 8 MiB from 64 MiB on (68 MiB of 2^17 22.8 ->
+//    21.8, 124 MiB 46.2 -> 41.4, 204 MiB of 2^18 67.4 -> 67.5), float32
+//    rows of 256 KiB to 4 MiB from 256 MiB on at b = 7 (330 MiB of 2^17 128.6
+//    -> 117.2, 488 MiB of 2^16 179.4 -> 172.7), fused levels up to five on
+//    complex128 rows of 1 to 8 MiB from 128 MiB on (152 MiB of 2^17 57.0 ->
+//    51.7, 216 MiB of 2^19 82.6 -> 75.0).  For complex64 the same gained 7%
+//    or lost 6% with the buffers' places, and is left.
+//  - Fused levels to 18 MiB on rectangular tiles at b = 6, smaller
+//    workgroups (complex64 16 MiB, five levels 8.1 -> 6.6; complex128 2^20,
+//    four 8.2 -> 6.8), and at 24 to 40 MiB (two levels and fewer from 30) with
+//    plain accesses, whose stores the L2s still hold there (complex64 2^22,
+//    six levels 15.1 -> 11.6, one 12.1 -> 11.4; 28 MiB with one would lose 9.8
+//    -> 10.3, 52 MiB 18.7 -> 23).
+PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint, int stages,
+                      const DeviceInfo& dev) {
+  PlanFields f;
+  if ((kind != kKindOutofplace && kind != kKindDitOutofplace) || dev.cus != 256 ||
+      !arch_matches("gfx950", dev.arch) || user_rows_apply(kind, s, footprint, dev))
+    return f;
+  auto set = [&f](int b, int variant, int order, int xcd, int hints) {
+    f.b = b;
+    f.variant = variant;
+    f.order = order;
+    f.xcd = xcd;
+    f.hints = hints;
+  };
+  const uint64_t mib = 1ull << 20, row = (uint64_t)s << k;
+  const bool many = rows >= 2 && row >= mib / 4 && row <= 8 * mib;
+  if (kind == kKindOutofplace) {
+    if (many && s == 16 && row >= mib && footprint >= 64 * mib) set(5, 1, 3, 2, 4);
+    if (many && s == 4 && row <= 4 * mib && footprint >= 256 * mib) set(7, 1, 1, 2, 4);
+    return f;
+  }
+  if (many && s == 16 && row >= mib && stages <= 5 && footprint >= 128 * mib) {
+    set(5, 1, 3, 2, 4);
+  } else if (footprint <= 18 * mib) {
+    if (s == 8 && (k >= 12 || (k == 11 && stages >= 3))) set(6, 2, 3, 2, 4);
+    if (s == 16 && k >= 12) set(6, 2, 1, 1, 4);
+  } else if (footprint >= (stages >= 3 ? 24 : 30) * mib && footprint <= 40 * mib) {
+    if (s == 8 && k >= 11) set(6, 2, 1, rows >= 2 ? 2 : 1, 1);
+    if (s == 16 && k >= 11) set(stages == 6 ? 6 : 5, 2, 1, 1, 1);
   }
   return f;
 }
@@ -519,8 +570,9 @@ bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_co
   const uint64_t row_bytes = ((uint64_t)s) << k;
   const uint64_t rows_u = rows > 0 ? (uint64_t)rows : 1u;
   const uint64_t footprint = row_bytes > UINT64_MAX / rows_u ? UINT64_MAX : row_bytes * rows_u;
-  const PlanFields tp =
-      table_plan(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, 0, 0, footprint, d);
+  const int kind = mode == kModeInplace ? kKindInplace : kKindOutofplace;
+  const PlanFields tp = table_plan(kind, s, 0, 0, footprint, d,
+                                   bytes_rule(kind, s, k, rows_u, footprint, 0, d));
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
                                          : (te.xcd_remap ? te.xcd_remap : (tp.xcd ? tp.xcd : 1));
@@ -1048,7 +1100,8 @@ bitrev_status_t bitrev_dit_stages_ex(const void* src, void* dst, int log2n, int6
   if (st != BITREV_SUCCESS) return st;
   const int kind = inplace ? kKindDitInplace : kKindDitOutofplace;
   const uint64_t footprint = n * s * (uint64_t)rows;
-  const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d);
+  const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages, d);
+  const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d, rule);
   int b;
   if (cfg && cfg->tile_bits) {
     b = cfg->tile_bits;  // forced: must hold the levels and fit (a
@@ -1075,7 +1128,7 @@ bitrev_status_t bitrev_dit_stages_ex(const void* src, void* dst, int log2n, int6
   a.t.items_per_seg = inplace ? pair_count(m) : (1ull << m);
   a.t.total_items = a.t.items_per_seg * (uint64_t)rows;
   a.t.seg_elems = n;
-  const PlanFields tp = table_plan(kind, (int)s, 0, b, footprint, d);
+  const PlanFields tp = table_plan(kind, (int)s, 0, b, footprint, d, rule);
   // rectangular tiles out of place (variant 2: source rows of 2^(b-1)
   // elements, 3: of 2^(b-2); b = 5 or 6, 16-byte aligned arrays)
   const int dvar = (cfg && cfg->variant) ? cfg->variant : (tp.variant ? tp.variant : 1);

@@ -352,10 +352,10 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
   return f;
 }
 
-// What the bytes and rows of an out-of-place launch on MI355X decide before
-// the table, whose rows know only powers of two and were measured on single
-// arrays (its choices stay wherever nothing is set here).  Kernel us, three
-// states in turn, before -> now.
+// What the bytes and rows of a launch on MI355X decide before the table, whose
+// rows know only powers of two and were measured on single arrays (its choices
+// stay wherever nothing is set here).  Kernel us, three states in turn, before
+// -> now.
 //  - Several rows, in dispatch order, which walks the rows one after the
 //    other where contiguous XCD ranges keep eight distant rows in flight:
 //    complex128 rows of 1 to 8 MiB from 64 MiB on (68 MiB of 2^17 22.8 ->
@@ -365,18 +365,27 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //    complex128 rows of 1 to 8 MiB from 128 MiB on (152 MiB of 2^17 57.0 ->
 //    51.7, 216 MiB of 2^19 82.6 -> 75.0).  For complex64 the same gained 7%
 //    or lost 6% with the buffers' places, and is left.
-//  - Fused levels to 18 MiB on rectangular tiles at b = 6, smaller
-//    workgroups (complex64 16 MiB, five levels 8.1 -> 6.6; complex128 2^20,
-//    four 8.2 -> 6.8), and at 24 to 40 MiB (two levels and fewer from 30) with
-//    plain accesses, whose stores the L2s still hold there (complex64 2^22,
-//    six levels 15.1 -> 11.6, one 12.1 -> 11.4; 28 MiB with one would lose 9.8
-//    -> 10.3, 52 MiB 18.7 -> 23).
+//  - Several rows of 40 to 64 MiB out of place by the one-item kernels: their
+//    write-through stores, where the table's pipelined kernels at 32 MiB keep
+//    plain ones (44 MiB of 2^16: complex64 16.8 -> 15.9, float32 17.1 -> 16.0,
+//    uint8 17.8 -> 16.5).  In place the wide pipelined tiles stay where a single
+//    array takes narrower ones, which lose there (float32 40 MiB of 2^17 13.2,
+//    narrower 13.7; complex64 31 MiB 10.6, 10.7; complex128 19.5 MiB of 2^14
+//    7.8, 8.4, 56 MiB 18.1, 18.5).
+//  - Fused levels from 12 to 16 MiB on rectangular tiles at b = 6, smaller
+//    workgroups (complex64 16 MiB, five levels 8.0 -> 6.5; complex128 2^20,
+//    four 8.3 -> 6.9), complex64 with two levels and more to 18 MiB and with
+//    five from 6 MiB (10 MiB of 2^14 6.2 -> 5.4).  Outside those lines they
+//    lose (17 MiB of complex128 2^14 7.5 -> 8.4, 4 MiB 3.5 -> 4.2; one
+//    complex64 level at 8 MiB 4.1 -> 4.4).
+//  - Six complex64 levels at 24 to 40 MiB with plain accesses, whose stores the
+//    L2s still hold there (2^22 15.0 -> 12.4, from cold caches 18.3 -> 18.2).
+//    Fewer gain 1 to 8% so and lose up to 14% from cold caches (one level 15.5
+//    -> 18.0): left to the table.
 PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint, int stages,
                       const DeviceInfo& dev) {
   PlanFields f;
-  if ((kind != kKindOutofplace && kind != kKindDitOutofplace) || dev.cus != 256 ||
-      !arch_matches("gfx950", dev.arch) || user_rows_apply(kind, s, footprint, dev))
-    return f;
+  if (kind == kKindDitInplace || dev.cus != 256 || !arch_matches("gfx950", dev.arch)) return f;
   auto set = [&f](int b, int variant, int order, int xcd, int hints) {
     f.b = b;
     f.variant = variant;
@@ -386,21 +395,31 @@ PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint,
   };
   const uint64_t mib = 1ull << 20, row = (uint64_t)s << k;
   const bool many = rows >= 2 && row >= mib / 4 && row <= 8 * mib;
-  if (kind == kKindOutofplace) {
+  if (kind == kKindInplace) {
+    const int c = footprint_class(footprint);
+    if (rows >= 2 && ((s == 4 && c == 25) || (s == 8 && c == 24) ||
+                      (s == 16 && footprint > 18 * mib && c <= 25)))
+      set(s == 4 ? 6 : 5, 2, 1, 2, 1);
+  } else if (kind == kKindOutofplace) {
+    if (rows >= 2 && footprint >= 40 * mib && footprint < 64 * mib) {
+      if (s <= 4) set(s == 1 ? 7 : 6, 1, 1, 1, 4);
+      if (s >= 8) set(5, 1, 2, 2, 4);
+    }
     if (many && s == 16 && row >= mib && footprint >= 64 * mib) set(5, 1, 3, 2, 4);
     if (many && s == 4 && row <= 4 * mib && footprint >= 256 * mib) set(7, 1, 1, 2, 4);
-    return f;
-  }
-  if (many && s == 16 && row >= mib && stages <= 5 && footprint >= 128 * mib) {
+  } else if (many && s == 16 && row >= mib && stages <= 5 && footprint >= 128 * mib) {
     set(5, 1, 3, 2, 4);
   } else if (footprint <= 18 * mib) {
-    if (s == 8 && (k >= 12 || (k == 11 && stages >= 3))) set(6, 2, 3, 2, 4);
-    if (s == 16 && k >= 12) set(6, 2, 1, 1, 4);
-  } else if (footprint >= (stages >= 3 ? 24 : 30) * mib && footprint <= 40 * mib) {
-    if (s == 8 && k >= 11) set(6, 2, 1, rows >= 2 ? 2 : 1, 1);
-    if (s == 16 && k >= 11) set(stages == 6 ? 6 : 5, 2, 1, 1, 1);
+    const bool large = footprint >= 12 * mib, one = stages == 1;
+    if (s == 8 && (k >= 12 || (k == 11 && large)) &&
+        (stages == 5 || (large && k >= 12 && (!one || footprint <= 16 * mib))) &&
+        footprint >= 6 * mib)
+      set(6, 2, 3, 2, 4);
+    if (s == 16 && k >= 12 && large && footprint <= 16 * mib) set(6, 2, 1, 1, 4);
+  } else if (footprint >= 24 * mib && footprint <= 40 * mib && s == 8 && k >= 11 && stages == 6) {
+    set(6, 2, 1, rows >= 2 ? 2 : 1, 1);
   }
-  return f;
+  return f.b && user_rows_apply(kind, s, footprint, dev) ? PlanFields() : f;
 }
 
 // ---------------------------------------------------------------------------
@@ -500,14 +519,19 @@ struct Plan {
 // whose accesses stay 4-byte aligned: true and *p filled where it is taken,
 // given the tile plan *p.  The lines, each with both sides measured (kernel
 // time, three matrices in turn):
-//  - rows of at most 32 KiB; of 64 KiB only off the 16-byte grid, where the
-//    tile kernels move single elements (float32 2^14 at a pitch of n + 2,
-//    32 MiB: 15.6 -> 11.4 us; aligned complex64 2^13: 10.7 against 11.1);
+//  - rows of at most 16 KiB, from 8 KiB on only at 64 MiB and more (complex64
+//    2^11 128 MiB 43.1 -> 41.4, 36 MiB 12.2 against 12.6; rows of 32 KiB lose
+//    1-8%); off the 16-byte grid, where the tile kernels move single elements,
+//    rows of up to 64 KiB (float32 2^14 at a pitch of n + 2, 32 MiB: 15.6 ->
+//    11.4 us);
 //  - where the tile plan has one tile per row (k = 2b), its accesses are
-//    linear too: it stays from 4 KiB rows (float32 2^10 8 MiB: 4.35 against
-//    4.56 us, complex128 2^10 128 MiB: 42.3 against 43.2) and, at 64 MiB
-//    and more, from 1 KiB rows of b >= 4 (float32 2^8: 64 MiB 20.9 -> 19.8,
-//    but 96 MiB 31.2 against 32.9; below 64 MiB 12.2 -> 10.5 at 32 MiB);
+//    linear too: it stays from 2 KiB rows (complex64 2^8 33 MiB out of place:
+//    10.8 against 11.4, int16 2^10 12 MiB 5.8 against 6.2), of bytes from 1 KiB
+//    rows and, at 64 MiB and more, from 1 KiB rows of b >= 4 (float32 2^8: 64
+//    MiB 20.9 -> 19.8, but 96 MiB 31.2 against 32.9; 12.2 -> 10.5 at 32 MiB);
+//  - the gathers of rows of 16 bytes and more from 512 KiB on: their four
+//    vectors per thread are a serial chain that costs 1 us from cold caches
+//    (uint8 2^6 0.3 MiB 6.1 against 7.1; at 2.5 MiB 8.6 -> 7.8);
 //  - bytes beyond 8 KiB rows stay: the gather's lanes then share LDS banks
 //    (2^14: 12.0 against 21.1 us).
 // Write-through stores with streaming loads from 64 MiB (complex64 2^10 64
@@ -524,8 +548,11 @@ bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool 
   const bool aligned = align == 16;
   if (rb > (aligned ? 32768u : 65536u) || (s == 1 && k > 13)) return false;
   const bool linear_tile = p->path == BITREV_PATH_TILE && p->m == 0 && p->vec && p->b >= 4;
-  if (linear_tile && (rb >= 4096 || (rb >= 1024 && footprint >= (64ull << 20)))) return false;
+  if (linear_tile && (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20)))))
+    return false;
+  if (aligned && rb >= 8192 && (rb > 16384 || (s > 1 && footprint < (64ull << 20)))) return false;
   const bool gather = s == 1 || k < 2 * c;
+  if (gather && rb >= 16 && contiguous && footprint < (512u << 10)) return false;
   int lb;
   if (gather) {
     lb = s > 1 ? 14 : rb > 4096 ? 13 : 12;
@@ -639,20 +666,28 @@ bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_co
 bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, uint64_t src_pitch,
                            uint64_t dst_pitch, const bitrev_config_t* cfg, size_t align,
                            const DeviceInfo& d, bool have_device, Plan* p) {
-  const bitrev_status_t st = plan_tiles(mode, k, s, rows, cfg, align, d, have_device, p);
-  if (st != BITREV_SUCCESS || p->path == BITREV_PATH_NONE || rows < 2 || k > 16 ||
-      config_set(cfg))
-    return st;
+  const auto tiles = [&] { return plan_tiles(mode, k, s, rows, cfg, align, d, have_device, p); };
+  if (rows < 2 || k > 16 || (mode == kModeInplace && k <= 1) || config_set(cfg)) return tiles();
   const TuneEntry te = tune_lookup(mode, s, k);
-  if (te.tile_bits || te.wg_per_cu || te.order || te.variant || te.xcd_remap || te.cache_hints)
-    return st;
   const uint64_t n = 1ull << k, footprint = (n * (uint64_t)s) * (uint64_t)rows;
-  if (user_rows_apply(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, footprint, d))
-    return st;
+  if (te.tile_bits || te.wg_per_cu || te.order || te.variant || te.xcd_remap || te.cache_hints ||
+      (uint64_t)rows > (1ull << 62) >> k ||
+      user_rows_apply(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, footprint, d))
+    return tiles();
   const bool contiguous = src_pitch == n && dst_pitch == n;
   const bool whole_lines = contiguous || ((src_pitch * s) % 64 == 0 && (dst_pitch * s) % 64 == 0);
-  plan_rows(k, s, (uint64_t)rows, align, contiguous, whole_lines, footprint, p);
-  return st;
+  // the tile plan is made first only where it may be one linear tile per row
+  *p = Plan();
+  const uint64_t rb = n * (uint64_t)s;
+  const bool ask_tiles = k >= 8 && k % 2 == 0 &&
+                         (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20))));
+  if (ask_tiles) {
+    const bitrev_status_t st = tiles();
+    if (st != BITREV_SUCCESS) return st;
+  }
+  if (plan_rows(k, s, (uint64_t)rows, align, contiguous, whole_lines, footprint, p) || ask_tiles)
+    return BITREV_SUCCESS;
+  return tiles();
 }
 
 // Workgroups of the batched kernel that fit on one CU at once: limited by

@@ -31,8 +31,12 @@ template <int S, int H> hipError_t run_rows_s(const RowsLaunch& a, hipStream_t s
         if constexpr (S == 16) return run_rows<S, 13, H>(a, st);
         break;
       case 14: return run_rows<S, 14, H>(a, st);
-      case 15: return run_rows<S, 15, H>(a, st);
-      case 16: return run_rows<S, 16, H>(a, st);
+      case 15:  // longer rows only off the 16-byte grid, with plain stores
+        if constexpr (H == kHintPlain) return run_rows<S, 15, H>(a, st);
+        break;
+      case 16:
+        if constexpr (H == kHintPlain) return run_rows<S, 16, H>(a, st);
+        break;
     }
   }
   return hipErrorInvalidValue;

@@ -57,6 +57,18 @@ def test_rows(s, k, rows):
     assert_bytes_equal(to_host_bytes(y), oracle.rows(host, k, s), "s=%d k=%d rows=%d" % (s, k, rows))
 
 
+@pytest.mark.parametrize("s,k,rows", [(1, 16, 641), (2, 15, 703), (4, 17, 97), (8, 16, 81),
+                                      (16, 14, 190), (8, 16, 33), (16, 14, 78), (16, 15, 33)])
+@pytest.mark.parametrize("inplace", (False, True))
+def test_rows_of_16_to_64_mib(s, k, rows, inplace):
+    host = workloads.byte_pattern((rows << k) * s, seed=k + rows)
+    x = torch.from_numpy(host).cuda().view(
+        {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64, 16: torch.complex128}[s])
+    y = x if inplace else torch.empty_like(x)
+    br.bitrev_rows(x, y, k)
+    assert_bytes_equal(to_host_bytes(y), oracle.rows(host, k, s), "s=%d k=%d rows=%d" % (s, k, rows))
+
+
 def test_the_plans_on_both_sides_of_the_lines():
     oop = br.MODE_OUTOFPLACE
     at = lambda k, s, rows, mode=oop: br.bitrev_plan_query(k, s, rows=rows, mode=mode)  # noqa: E731
@@ -64,5 +76,9 @@ def test_the_plans_on_both_sides_of_the_lines():
     assert at(16, 4, 1024)["tile_bits"] == 7 and at(16, 4, 1024)["order"] == 1
     assert at(16, 4, 1023)["tile_bits"] == 6
     assert at(24, 16, 1)["order"] == 2  # one array: the table
+    assert at(16, 8, 80)["variant"] == 1 and at(16, 8, 79)["variant"] == 2
+    assert at(16, 8, 127)["cache_hints"] == br.HINTS_STREAM_WRITE_THROUGH
+    assert at(21, 8, 1, br.MODE_INPLACE)["tile_bits"] == 4
+    assert at(16, 8, 33, br.MODE_INPLACE)["tile_bits"] == 5
     forced = br.bitrev_plan_query(16, 16, rows=64, mode=oop, order=2, xcd_remap=1)
     assert (forced["order"], forced["xcd_remap"]) == (2, 1)

@@ -68,8 +68,8 @@ def test_base_off_the_16_byte_grid(s, shift):
                 _check(s, k, 21, 1 << k, shift, inplace)
 
 
-@pytest.mark.parametrize("s,k", [(1, 3), (1, 9), (1, 13), (2, 2), (2, 7), (4, 3), (4, 9), (4, 13), (8, 0),
-                                 (8, 5), (8, 12), (16, 4), (16, 9), (16, 11)])
+@pytest.mark.parametrize("s,k", [(1, 3), (1, 9), (1, 13), (2, 2), (2, 7), (4, 3), (4, 9), (4, 11), (8, 0),
+                                 (8, 5), (8, 11), (16, 4), (16, 9)])
 def test_write_through_form(s, k):
     """Footprints from 64 MiB (32 MiB for the gathers of 1 and 2 bytes) take
     streaming loads and write-through stores; an odd number of rows."""
@@ -78,4 +78,14 @@ def test_write_through_form(s, k):
     assert p["path"] == br.PATH_ROWS and p["cache_hints"] == br.HINTS_STREAM_WRITE_THROUGH
     for inplace in (False, True):
         if not (inplace and k <= 1):
+            _check(s, k, rows, 1 << k, 0, inplace)
+
+
+@pytest.mark.parametrize("s,k", [(1, 4), (1, 7), (2, 3), (2, 5), (4, 2), (4, 3)])
+def test_contiguous_gathers(s, k):
+    """Rows of 16 bytes and more gather from 512 KiB on; one row to either side."""
+    for rows in ((512 << 10) // (s << k) - 1, (512 << 10) // (s << k) + 1):
+        p = br.bitrev_plan_query(k, s, rows=rows, mode=br.MODE_OUTOFPLACE)
+        assert (p["path"] == br.PATH_ROWS) == (rows * (s << k) > 512 << 10)
+        for inplace in (False, True):
             _check(s, k, rows, 1 << k, 0, inplace)

@@ -48,8 +48,9 @@ def test_transposed_vectors_are_the_reversal(c):
 
 
 def test_which_calls_take_it():
-    """Only several rows, with nothing forced, of at most 32 KiB, and not where
-    the tile plan has one linear tile per row."""
+    """Only several rows, with nothing forced, of at most 16 KiB (from 8 KiB on at
+    64 MiB and more, bytes at any), not where the tile plan has one linear tile
+    per row, and not the gathers of small launches."""
     for s, k, mode in itertools.product((1, 2, 4, 8, 16), range(0, 18), (0, 1)):
         one = br.bitrev_plan_query(k, s, rows=1, mode=mode)
         assert one["path"] != br.PATH_ROWS
@@ -60,14 +61,20 @@ def test_which_calls_take_it():
             if mode == 0 and k <= 1:
                 assert p["path"] == br.PATH_NONE
                 continue
-            if (s << k) > 32768 or (s == 1 and k > 13):
-                assert p["path"] == br.PATH_TILE
-                continue
+            rb, footprint = s << k, rows * s << k
+            small = footprint < 64 << 20
             whole = br.bitrev_plan_query(k, s, rows=rows, mode=mode, xcd_remap=2)
             linear = (whole["path"] == br.PATH_TILE and whole["mid_bits"] == 0
                       and whole["tile_bits"] >= 4
-                      and ((s << k) >= 4096 or ((s << k) >= 1024 and (rows * s << k) >= 64 << 20)))
-            assert p["path"] == (br.PATH_TILE if linear else br.PATH_ROWS), (s, k, rows, mode)
+                      and (rb >= 2048 or (rb == 1024 and (s == 1 or not small))))
+            gather = s == 1 or 1 << k < (16 // s) ** 2
+            tiles = (linear or rb > 16384 or (s == 1 and k > 13)
+                     or (s > 1 and rb >= 8192 and small)
+                     or (gather and rb >= 16 and footprint < 512 << 10))
+            if tiles:
+                assert p["path"] in (br.PATH_TILE, br.PATH_WAVE), (s, k, rows, mode)
+            else:
+                assert p["path"] == br.PATH_ROWS, (s, k, rows, mode)
             if p["path"] == br.PATH_ROWS:
                 assert p["lds_bytes"] >= s << k
                 assert p["work_items"] * p["lds_bytes"] >= rows * s << k

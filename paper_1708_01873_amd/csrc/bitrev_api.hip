@@ -519,7 +519,7 @@ struct Plan {
 // whose accesses stay 4-byte aligned: true and *p filled where it is taken,
 // given the tile plan *p.  The lines, each with both sides measured (kernel
 // time, three matrices in turn):
-//  - rows of at most 16 KiB, from 8 KiB on only at 64 MiB and more (complex64
+//  - rows of at most 16 KiB, from 8 KiB on only bytes or 64 MiB (complex64
 //    2^11 128 MiB 43.1 -> 41.4, 36 MiB 12.2 against 12.6; rows of 32 KiB lose
 //    1-8%); off the 16-byte grid, where the tile kernels move single elements,
 //    rows of up to 64 KiB (float32 2^14 at a pitch of n + 2, 32 MiB: 15.6 ->
@@ -529,11 +529,10 @@ struct Plan {
 //    10.8 against 11.4, int16 2^10 12 MiB 5.8 against 6.2), of bytes from 1 KiB
 //    rows and, at 64 MiB and more, from 1 KiB rows of b >= 4 (float32 2^8: 64
 //    MiB 20.9 -> 19.8, but 96 MiB 31.2 against 32.9; 12.2 -> 10.5 at 32 MiB);
-//  - the gathers of rows of 16 bytes and more from 512 KiB on: their four
-//    vectors per thread are a serial chain that costs 1 us from cold caches
-//    (uint8 2^6 0.3 MiB 6.1 against 7.1; at 2.5 MiB 8.6 -> 7.8);
-//  - bytes beyond 8 KiB rows stay: the gather's lanes then share LDS banks
-//    (2^14: 12.0 against 21.1 us).
+//  - the gathers of rows of 16 bytes and more from 512 KiB on, of shorter
+//    ones from 32 KiB: their four vectors per thread are a serial chain that
+//    costs 1 us from cold caches (uint8 2^6 0.3 MiB 6.1 against 7.1, at 2.5
+//    MiB 8.6 -> 7.8; 2^3 0.3 MiB 9.5 -> 7.2).
 // Write-through stores with streaming loads from 64 MiB (complex64 2^10 64
 // MiB 20.1 -> 19.6 us, 128 MiB 47.5 -> 42.4; at 32 MiB out of place 10.5
 // against 10.8) and for the gathers of 1- and 2-byte elements from 32 MiB
@@ -546,16 +545,16 @@ bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool 
   const int c = s == 16 ? 0 : s == 8 ? 1 : s == 4 ? 2 : s == 2 ? 3 : 4;
   if (rows < 2 || k > 16 || align < 4 || (rb < 16 && !contiguous)) return false;
   const bool aligned = align == 16;
-  if (rb > (aligned ? 32768u : 65536u) || (s == 1 && k > 13)) return false;
+  if (rb > 65536u) return false;
   const bool linear_tile = p->path == BITREV_PATH_TILE && p->m == 0 && p->vec && p->b >= 4;
   if (linear_tile && (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20)))))
     return false;
   if (aligned && rb >= 8192 && (rb > 16384 || (s > 1 && footprint < (64ull << 20)))) return false;
-  const bool gather = s == 1 || k < 2 * c;
-  if (gather && rb >= 16 && contiguous && footprint < (512u << 10)) return false;
+  const bool gather = k < 2 * c;
+  if (gather && contiguous && footprint < ((rb >= 16 ? 512u : 32u) << 10)) return false;
   int lb;
   if (gather) {
-    lb = s > 1 ? 14 : rb > 4096 ? 13 : 12;
+    lb = s > 1 ? 14 : 12;
   } else {
     lb = s == 16 ? 13 : 14;
     while ((1ull << lb) < rb) ++lb;
@@ -895,7 +894,9 @@ bitrev_status_t run_plain(const void* src, void* dst, int k, int64_t rows, size_
   if (st != BITREV_SUCCESS) return st;
   Plan p;
   size_t align = pointer_align(src, dst);
-  if (rows > 1) {
+  // (contiguous rows shorter than a vector are one run of bytes: 2^1 uint8, 40
+  // MiB, 899 us by single elements)
+  if (rows > 1 && !(src_stride == n && dst_stride == n && n * s < 16)) {
     const size_t sa = align_of(src_stride * s), da = align_of(dst_stride * s);
     if (sa < align) align = sa;
     if (da < align) align = da;

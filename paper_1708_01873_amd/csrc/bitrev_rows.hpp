@@ -81,7 +81,10 @@ template <int S> __device__ __forceinline__ void rows_transpose(const u32x4 (&a)
 // index [e | q | j] goes to [rev(j) | rev(q) | rev(e)], so output vector j is
 // vector [rev(j) | rev(q)] of the row.  One 16-byte LDS write and read per
 // vector turn the scattered vectors into linear runs.
-template <int S, int LB, int H>
+// LH: the hint of the loads, H that of the stores (both streaming forms bypass
+// the caches for a line the kernel touches once; a part of less than 64 bytes
+// shares its line with the next).
+template <int S, int LB, int H, int LH>
 __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, void* dst, int k,
                                                              uint64_t rows, uint64_t src_pitch,
                                                              uint64_t dst_pitch) {
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, v
         const char* p = in + r * src_pitch + q * 16u;
 #pragma unroll
         for (int e = 0; e < CE; ++e)
-          a[e] = ld_hint<H>(reinterpret_cast<const u32x4_a4*>(p + ((size_t)e << (w + 4))));
+          a[e] = ld_hint<LH>(reinterpret_cast<const u32x4_a4*>(p + ((size_t)e << (w + 4))));
         rows_transpose<S>(a, t);
         const uint32_t o = (r << lv) + rev_bits(q, w);
 #pragma unroll
@@ -125,10 +128,75 @@ __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, v
   }
 }
 
-// Rows shorter than k = 2 c, and all rows of bytes: a chunk of rows goes to
-// LDS as it is, and each output vector gathers its elements one by one (bytes
-// need sixteen vectors for a transpose in registers; the gather holds one, and
-// its lanes read neighbouring bytes up to k = 12).  The data are `nrun` runs of
+// Threads of a workgroup of k_rows_bytes: sixteen dwords each.
+__host__ __device__ constexpr int bytes_threads(int lb) { return 1 << (lb - 6); }
+
+// Rows of 2^k bytes, k >= 8.  Whole vectors at one offset of sixteen parts
+// would be 64 registers in and 64 out; a thread takes one dword of each part
+// instead: byte (e, q, j) of the index [e(4) | q | j(2)] goes to [rev(j) |
+// rev(q) | rev(e)], so the four bytes j of the sixteen dwords are four whole
+// output vectors, made by 4 x 4 byte transposes (two v_perm a dword).  A
+// wavefront reads 16 bytes of each part of a row at k = 8, 256 from k = 12 on;
+// below k = 8 the gather is better.
+// Bound by memory.  Against a gather of single bytes from LDS (64 byte reads
+// for each four vectors), three arrays in turn, us: 2^8 12.9 MiB 8.2 -> 6.8,
+// 2^9 29.5 MiB 13.4 -> 10.9, 2^11 34 MiB 12.9 -> 12.0 and 14.9 -> 11.6 out of
+// place, 2^13 38 MiB 16.0 -> 13.1 and 17.6 -> 12.7 (a copy of 38 MiB: 12.5).
+template <int LB, int H, int LH>
+__global__ __launch_bounds__(bytes_threads(LB)) void k_rows_bytes(const void* src, void* dst, int k,
+                                                                 uint64_t rows, uint64_t src_pitch,
+                                                                 uint64_t dst_pitch) {
+  constexpr int NT = bytes_threads(LB);
+  constexpr uint32_t CHV = 1u << (LB - 4);
+  __shared__ u32x4 lds[CHV];
+  const int w = k - 6, lv = k - 4;
+  const uint32_t vmask = (1u << lv) - 1u;
+  const uint32_t q = threadIdx.x & ((1u << w) - 1u), r = threadIdx.x >> w;
+  const uint32_t o = (r << lv) + rev_bits(q, w);
+  const uint64_t step = (uint64_t)gridDim.x * (CHV >> lv);
+  for (uint64_t row0 = (uint64_t)blockIdx.x * (CHV >> lv); row0 < rows; row0 += step) {
+    const uint32_t live = rows - row0 < (CHV >> lv) ? (uint32_t)(rows - row0) : CHV >> lv;
+    const char* in = static_cast<const char*>(src) + row0 * src_pitch;
+    char* out = static_cast<char*>(dst) + row0 * dst_pitch;
+    if (r < live) {
+      const char* p = in + r * src_pitch + q * 4u;
+      uint32_t a[16];
+      u32x4 t[4];
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        a[e] = ld_hint<LH>(reinterpret_cast<const uint32_t*>(p + ((size_t)e << lv)));
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {  // dword d of an output vector: bytes rev(4d + b), b = 0..3
+        constexpr int kRev[4] = {0, 2, 1, 3};
+        const uint32_t x0 = a[kRev[d]], x1 = a[8 + kRev[d]], x2 = a[4 + kRev[d]],
+                       x3 = a[12 + kRev[d]];
+        const uint32_t lo0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u);
+        const uint32_t lo1 = __builtin_amdgcn_perm(x3, x2, 0x05010400u);
+        const uint32_t hi0 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
+        const uint32_t hi1 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
+        t[0][d] = __builtin_amdgcn_perm(lo1, lo0, 0x05040100u);
+        t[1][d] = __builtin_amdgcn_perm(lo1, lo0, 0x07060302u);
+        t[2][d] = __builtin_amdgcn_perm(hi1, hi0, 0x05040100u);
+        t[3][d] = __builtin_amdgcn_perm(hi1, hi0, 0x07060302u);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) lds[rows_slot(o + ((uint32_t)crev(j, 2) << w))] = t[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t v = threadIdx.x + i * NT;
+      const uint32_t s = v >> lv;
+      if (s < live)
+        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + s * dst_pitch + (v & vmask) * 16u),
+                   (u32x4_a4)lds[rows_slot(v)]);
+    }
+    __syncthreads();
+  }
+}
+
+// Rows shorter than k = 2 c: a chunk of rows goes to LDS as it is, and each
+// output vector gathers its elements one by one.  The data are `nrun` runs of
 // 2^lr vectors, `pitch` bytes apart: the rows, or single vectors (lr = 0,
 // pitch 16) of contiguous rows shorter than a vector; the `tail` elements
 // after the last whole run move alone.

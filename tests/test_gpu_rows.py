@@ -89,3 +89,14 @@ def test_contiguous_gathers(s, k):
         assert (p["path"] == br.PATH_ROWS) == (rows * (s << k) > 512 << 10)
         for inplace in (False, True):
             _check(s, k, rows, 1 << k, 0, inplace)
+
+
+@pytest.mark.parametrize("k", range(8, 17))
+def test_bytes_by_dwords(k):
+    """Rows of bytes at pitches that keep 4-byte alignment, up to 64 KiB; rows
+    around one chunk."""
+    per = max(1, (1 << 14) >> k)
+    for rows in sorted({2, per + 1, 3 * per + 2}):
+        for pad in (4, 12, 16):
+            for inplace in (False, True):
+                _check(1, k, rows, (1 << k) + pad, 0, inplace)

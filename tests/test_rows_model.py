@@ -47,6 +47,22 @@ def test_transposed_vectors_are_the_reversal(c):
         assert np.array_equal(got, oracle.rev_table(k)), (c, k)
 
 
+@pytest.mark.parametrize("k", range(8, 17))
+def test_transposed_dwords_are_the_reversal(k):
+    """Bytes: one dword of each of sixteen parts, four whole output vectors."""
+    w = k - 6
+    row = np.arange(1 << k)
+    lds = {}
+    for q in range(1 << w):
+        a = [row[(e << (k - 4)) + 4 * q:][:4] for e in range(16)]
+        for j in range(4):
+            # dword d, byte b: parts rev(d), 8 + rev(d), 4 + rev(d), 12 + rev(d)
+            t = [a[(0, 8, 4, 12)[b] + (0, 2, 1, 3)[d]][j] for d in range(4) for b in range(4)]
+            lds[slot(rev(q, w) + (rev(j, 2) << w))] = t
+    got = np.concatenate([lds[slot(v)] for v in range(1 << (k - 4))])
+    assert np.array_equal(got, oracle.rev_table(k))
+
+
 def test_which_calls_take_it():
     """Only several rows, with nothing forced, of at most 16 KiB (from 8 KiB on at
     64 MiB and more, bytes at any), not where the tile plan has one linear tile
@@ -67,10 +83,10 @@ def test_which_calls_take_it():
             linear = (whole["path"] == br.PATH_TILE and whole["mid_bits"] == 0
                       and whole["tile_bits"] >= 4
                       and (rb >= 2048 or (rb == 1024 and (s == 1 or not small))))
-            gather = s == 1 or 1 << k < (16 // s) ** 2
+            gather = 1 << k < (16 // s) ** 2
             tiles = (linear or rb > 16384 or (s == 1 and k > 13)
                      or (s > 1 and rb >= 8192 and small)
-                     or (gather and rb >= 16 and footprint < 512 << 10))
+                     or (gather and footprint < (512 if rb >= 16 else 32) << 10))
             if tiles:
                 assert p["path"] in (br.PATH_TILE, br.PATH_WAVE), (s, k, rows, mode)
             else:

@@ -1429,14 +1429,15 @@ static bitrev_status_t run_batched(const void* src, void* data, int64_t data_ele
   a.data_elems = data_elems;
   a.ws = static_cast<int64_t*>(workspace);
   a.b = p.b;
-  // Arrays that move whole through LDS: those too short for a tile, and in
-  // batches of short arrays (under 16 KiB on average, no width forced) all up
-  // to 32 KiB (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500
-  // complex128 arrays of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
+  // Arrays that move whole through LDS: those too short for a tile and, no
+  // width forced, all up to 16 KiB (5000 complex128 arrays of 2^10 35.8 ->
+  // 28.8 us), in batches of short arrays (under 16 KiB on average) up to 32 KiB
+  // (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500 complex128 arrays
+  // of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
   a.whole = 2 * p.b - 1;
   const bool shorts = (uint64_t)data_elems / (uint64_t)num_arrays < 16384 / elem_size;
-  if (shorts && !(cfg && cfg->tile_bits))
-    while ((elem_size << (a.whole + 1)) <= 32768) ++a.whole;
+  if (!(cfg && cfg->tile_bits))
+    while ((elem_size << (a.whole + 1)) <= (shorts ? 32768u : 16384u)) ++a.whole;
   a.hints = (uint64_t)data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
   a.balanced = order_code(p.order);
   // one item per workgroup runs in dispatch order: contiguous XCD ranges walk

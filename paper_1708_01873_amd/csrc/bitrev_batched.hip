@@ -12,10 +12,13 @@ namespace {
 // Threads of a workgroup with 2^lb bytes of LDS: four 16-byte vectors each, 4
 // KiB a wavefront.
 constexpr int front_threads(int lb) { return 1 << (lb - 6); }
-// Arrays per workgroup of the whole-array part: short batches (32 KiB of LDS)
-// 8 (20000 float32 arrays of 2^4-2^12: 4 per workgroup 34.9 us, 8 30.8, 16
-// 33), longer arrays 2 (4 lost 1-2%).
+// Arrays per workgroup of the whole-array part, at most: short batches (32 KiB
+// of LDS) 8 (20000 float32 arrays of 2^4-2^12: 4 per workgroup 34.9 us, 8 30.8,
+// 16 33), longer arrays 2 (4 lost 1-2%).  Batches of fewer arrays than fill
+// kMinFrontBlocks workgroups so take fewer each (50 float32 arrays of 2^0-2^14
+// out of place by 8: 8.5 us, one by one 7.2).
 constexpr int front_arrays(int lb) { return lb == 15 ? 8 : 2; }
+constexpr int kMinFrontBlocks = 512;
 // Arrays per scan workgroup.
 constexpr int kArraysPerScan = 1024;
 constexpr int kMaxScanBlocks = 32;
@@ -29,6 +32,7 @@ struct BatchMeta {
   int b;      // tile width
   int whole;  // arrays of at most 2^whole elements move whole
   int oop;
+  int per;    // arrays per workgroup of the whole-array part
 };
 
 // Whether array a's metadata hold together: 2^log2n elements between its
@@ -155,9 +159,11 @@ __device__ __forceinline__ int64_t lane_value(int64_t v, int i) {
 }
 
 // One array of 2^k elements through LDS by NT threads, t of them, each moving
-// at most VPT vectors: k_rows' steps where a row has them, element by element
-// for bytes, for 2-byte elements off the 4-byte grid and for the rows of
-// k < 2 c too long for a wavefront's lanes.
+// at most VPT vectors: k_rows' and k_rows_bytes' steps where a row has them,
+// element by element for 1- and 2-byte elements off the 4-byte grid and for
+// the rows of k < 2 c too long for a wavefront's lanes.  The element loops
+// read eight at once, and the banks are spread (50 int16 arrays of 2^0-2^14:
+// 17.3 us one by one, 12.5 by eight, 7.6 with the spread and a workgroup each).
 template <int S, int NT, int VPT, int H, typename Sync>
 __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u32x4* lds,
                                             uint32_t t, Sync sync) {
@@ -192,6 +198,35 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
       return;
     }
   }
+  if constexpr (S == 1) {
+    if (k >= 8 && vec) {
+      constexpr int T = (VPT + 3) / 4;
+      const int w = k - 6, lv = k - 4;
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const uint32_t q = t + i * NT;
+        if (q < (1u << w)) {
+          uint32_t a[16];
+          u32x4 r[4];
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            a[e] = *reinterpret_cast<const uint32_t*>(in + q * 4u + ((uint32_t)e << lv));
+          bytes_transpose(a, r);
+          const uint32_t o = rev_bits(q, w);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) lds[rows_slot(o + ((uint32_t)crev(j, 2) << w))] = r[j];
+        }
+      }
+      sync();
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const uint32_t v = t + i * NT;
+        if (v < (1u << lv))
+          st_hint<H>(reinterpret_cast<u32x4_a4*>(out + v * 16u), (u32x4_a4)lds[rows_slot(v)]);
+      }
+      return;
+    }
+  }
   E* le = reinterpret_cast<E*>(lds);
   const uint32_t n = 1u << k;
   if (S < 4 && k >= C && vec) {
@@ -210,9 +245,34 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
     }
     return;
   }
-  for (uint32_t i = t; i < n; i += NT) le[i] = reinterpret_cast<const E*>(in)[i];
+  // element i's place: the lanes of the reversed read differ in i's top bits,
+  // which the XOR brings into the low ones, the banks
+  const int sh = k > 6 ? k - 6 : 1;
+  const auto at = [sh](uint32_t i) { return i ^ (i >> sh); };
+  constexpr int kAtOnce = 8;
+  const E* ein = reinterpret_cast<const E*>(in);
+  E* eout = reinterpret_cast<E*>(out);
+#pragma unroll 1
+  for (uint32_t i0 = t; i0 < n; i0 += kAtOnce * NT) {
+    E x[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u)
+      if (i0 + u * NT < n) x[u] = ein[i0 + u * NT];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u)
+      if (i0 + u * NT < n) le[at(i0 + u * NT)] = x[u];
+  }
   sync();
-  for (uint32_t i = t; i < n; i += NT) reinterpret_cast<E*>(out)[i] = le[rev_bits(i, k)];
+#pragma unroll 1
+  for (uint32_t i0 = t; i0 < n; i0 += kAtOnce * NT) {
+    E x[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u)
+      if (i0 + u * NT < n) x[u] = le[at(rev_bits(i0 + u * NT, k))];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u)
+      if (i0 + u * NT < n) eout[i0 + u * NT] = x[u];
+  }
 }
 
 // The scan workgroups, then workgroups of front_arrays consecutive arrays:
@@ -234,23 +294,26 @@ __global__ __launch_bounds__(front_threads(LB)) void k_batched_front(const void*
     batched_scan<NT>(m, ws, (int)blockIdx.x, scan_blocks);
     return;
   }
-  constexpr int kWaveBytes = 4096, kArrays = front_arrays(LB);
+  constexpr int kWaveBytes = 4096;
   __shared__ u32x4 lds[1 << (LB - 4)];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
   const char* in = static_cast<const char*>(m.oop ? src : data);
   char* out = static_cast<char*>(data);
-  const int64_t step = (int64_t)(gridDim.x - (uint32_t)scan_blocks) * kArrays;
-  for (int64_t a0 = (int64_t)(blockIdx.x - (uint32_t)scan_blocks) * kArrays; a0 < m.num;
+  const int64_t step = (int64_t)(gridDim.x - (uint32_t)scan_blocks) * m.per;
+  for (int64_t a0 = (int64_t)(blockIdx.x - (uint32_t)scan_blocks) * m.per; a0 < m.num;
        a0 += step) {
     int k = -1;
     int64_t o0 = 0;
-    if (lane < kArrays && a0 + lane < m.num) {
+    if (lane < (uint32_t)m.per && a0 + lane < m.num) {
       k = m.log2n[a0 + lane];
       o0 = m.offsets[a0 + lane];
       if (!array_ok(m, k, o0, m.offsets[a0 + lane + 1]) || k > m.whole || (k <= 1 && !m.oop)) k = -1;
     }
-    const bool one_wave = k >= 0 && ((int64_t)S << k) <= kWaveBytes;
+    // (element by element, a wavefront alone would take 4 KiB in 32 or 64 steps)
+    const bool steps = S < 4 && k > 9 && ((reinterpret_cast<uintptr_t>(in) + S * o0) |
+                                          (reinterpret_cast<uintptr_t>(out) + S * o0)) & 3u;
+    const bool one_wave = k >= 0 && ((int64_t)S << k) <= kWaveBytes && !steps;
     uint64_t small = __ballot(one_wave), large = __ballot(k >= 0 && !one_wave);
     while (large) {
       const int i = __builtin_ctzll(large);
@@ -293,8 +356,9 @@ template <int S, int LB> hipError_t run_front(const BatchedLaunch& a, hipStream_
   m.oop = a.src != nullptr ? 1 : 0;
   const int64_t want = (a.num + kArraysPerScan - 1) / kArraysPerScan;
   const int scan = (int)(want < kMaxScanBlocks ? want : kMaxScanBlocks);
-  constexpr int kArrays = front_arrays(LB);
-  const int64_t blocks = (a.num + kArrays - 1) / kArrays;
+  const int64_t few = a.num / kMinFrontBlocks;
+  m.per = few < 1 ? 1 : few < front_arrays(LB) ? (int)few : front_arrays(LB);
+  const int64_t blocks = (a.num + m.per - 1) / m.per;
   const uint32_t grid = (uint32_t)scan + (uint32_t)(blocks < (1 << 20) ? blocks : (1 << 20));
   if (a.hints == kHintStreamWriteThrough) {
     hipLaunchKernelGGL((k_batched_front<S, LB, kHintStreamWriteThrough>), dim3(grid),

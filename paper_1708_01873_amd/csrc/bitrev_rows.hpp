@@ -131,6 +131,23 @@ __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, v
 // Threads of a workgroup of k_rows_bytes: sixteen dwords each.
 __host__ __device__ constexpr int bytes_threads(int lb) { return 1 << (lb - 6); }
 
+// The sixteen dwords a[e] of four bytes, as the four vectors t[j] with byte
+// t[j][rev(e)] = a[e][j] (e of four bits): 4 x 4 byte transposes.
+__device__ __forceinline__ void bytes_transpose(const uint32_t (&a)[16], u32x4 (&t)[4]) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {  // dword d of an output vector: bytes rev(4d + b), b = 0..3
+    const int e = crev(d, 2);
+    const uint32_t lo0 = __builtin_amdgcn_perm(a[8 + e], a[e], 0x05010400u);
+    const uint32_t lo1 = __builtin_amdgcn_perm(a[12 + e], a[4 + e], 0x05010400u);
+    const uint32_t hi0 = __builtin_amdgcn_perm(a[8 + e], a[e], 0x07030602u);
+    const uint32_t hi1 = __builtin_amdgcn_perm(a[12 + e], a[4 + e], 0x07030602u);
+    t[0][d] = __builtin_amdgcn_perm(lo1, lo0, 0x05040100u);
+    t[1][d] = __builtin_amdgcn_perm(lo1, lo0, 0x07060302u);
+    t[2][d] = __builtin_amdgcn_perm(hi1, hi0, 0x05040100u);
+    t[3][d] = __builtin_amdgcn_perm(hi1, hi0, 0x07060302u);
+  }
+}
+
 // Rows of 2^k bytes, k >= 8.  Whole vectors at one offset of sixteen parts
 // would be 64 registers in and 64 out; a thread takes one dword of each part
 // instead: byte (e, q, j) of the index [e(4) | q | j(2)] goes to [rev(j) |
@@ -165,20 +182,7 @@ __global__ __launch_bounds__(bytes_threads(LB)) void k_rows_bytes(const void* sr
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         a[e] = ld_hint<LH>(reinterpret_cast<const uint32_t*>(p + ((size_t)e << lv)));
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {  // dword d of an output vector: bytes rev(4d + b), b = 0..3
-        constexpr int kRev[4] = {0, 2, 1, 3};
-        const uint32_t x0 = a[kRev[d]], x1 = a[8 + kRev[d]], x2 = a[4 + kRev[d]],
-                       x3 = a[12 + kRev[d]];
-        const uint32_t lo0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u);
-        const uint32_t lo1 = __builtin_amdgcn_perm(x3, x2, 0x05010400u);
-        const uint32_t hi0 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
-        const uint32_t hi1 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
-        t[0][d] = __builtin_amdgcn_perm(lo1, lo0, 0x05040100u);
-        t[1][d] = __builtin_amdgcn_perm(lo1, lo0, 0x07060302u);
-        t[2][d] = __builtin_amdgcn_perm(hi1, hi0, 0x05040100u);
-        t[3][d] = __builtin_amdgcn_perm(hi1, hi0, 0x07060302u);
-      }
+      bytes_transpose(a, t);
 #pragma unroll
       for (int j = 0; j < 4; ++j) lds[rows_slot(o + ((uint32_t)crev(j, 2) << w))] = t[j];
     }

@@ -108,3 +108,22 @@ def test_write_through_form():
         got, err = _run(host, 8, offsets, ks, oop)
         assert_bytes_equal(got, want, "oop=%s" % oop)
         assert err == (0, -1)
+
+
+@pytest.mark.parametrize("oop", (False, True))
+@pytest.mark.parametrize("s,k0", [(1, 4), (1, 2), (2, 3), (2, 1)])
+def test_arrays_on_the_4_byte_grid(s, k0, oop):
+    """1- and 2-byte arrays whose offsets keep 4 bytes: the register transposes
+    at every length, several per workgroup and (few arrays) one."""
+    kmax = 16 if s == 1 else 15
+    for copies in (1, 90):
+        ks = np.concatenate([np.arange(k0, kmax + 1)] + [np.arange(k0, kmax - 4)] * copies)
+        ks = ks.astype(np.int32)
+        np.random.default_rng(k0).shuffle(ks)
+        offsets = _offsets(ks)
+        host = workloads.byte_pattern(int(offsets[-1]) * s, seed=s + copies)
+        want = host.copy()
+        oracle.batched(want, offsets, ks, s)
+        got, err = _run(host, s, offsets, ks, oop)
+        assert_bytes_equal(got, want, "s=%d k0=%d oop=%s copies=%d" % (s, k0, oop, copies))
+        assert err == (0, -1)

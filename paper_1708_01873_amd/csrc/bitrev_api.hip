@@ -372,6 +372,11 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //    array takes narrower ones, which lose there (float32 40 MiB of 2^17 13.2,
 //    narrower 13.7; complex64 31 MiB 10.6, 10.7; complex128 19.5 MiB of 2^14
 //    7.8, 8.4, 56 MiB 18.1, 18.5).
+//  - Off the 16-byte grid, and rows at a padded pitch, keep the wide pipelined
+//    tiles to 64 MiB (out of place to 32), and the table beyond: single
+//    elements want them (int16 2^14 at n + 1, 6.7 MiB 5.0, narrower 6.0), and
+//    the narrower ones gain most where a pitch of a power of two maps rows to
+//    the same channels (complex128 2^16 at n + 4, 6 MiB 4.1, narrower 4.9).
 //  - Fused levels from 12 to 16 MiB on rectangular tiles at b = 6, smaller
 //    workgroups (complex64 16 MiB, five levels 8.0 -> 6.5; complex128 2^20,
 //    four 8.3 -> 6.9), complex64 with two levels and more to 18 MiB and with
@@ -383,7 +388,7 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //    Fewer gain 1 to 8% so and lose up to 14% from cold caches (one level 15.5
 //    -> 18.0): left to the table.
 PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint, int stages,
-                      const DeviceInfo& dev) {
+                      bool linear, const DeviceInfo& dev) {
   PlanFields f;
   if (kind == kKindDitInplace || dev.cus != 256 || !arch_matches("gfx950", dev.arch)) return f;
   auto set = [&f](int b, int variant, int order, int xcd, int hints) {
@@ -395,8 +400,12 @@ PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint,
   };
   const uint64_t mib = 1ull << 20, row = (uint64_t)s << k;
   const bool many = rows >= 2 && row >= mib / 4 && row <= 8 * mib;
-  if (kind == kKindInplace) {
-    const int c = footprint_class(footprint);
+  const int c = footprint_class(footprint);
+  if (stages == 0 && !linear) {
+    if (kind == kKindInplace && c <= 25 && s != 1) set(s == 2 ? 7 : s == 4 ? 6 : 5, 2, 1, 2, 1);
+    if (kind == kKindOutofplace && s == 2 && c <= 24) set(7, 2, 2, 2, 1);
+    if (kind == kKindOutofplace && s == 16 && c <= 24) set(5, 2, 2, 2, 1);
+  } else if (kind == kKindInplace) {
     if (rows >= 2 && ((s == 4 && c == 25) || (s == 8 && c == 24) ||
                       (s == 16 && footprint > 18 * mib && c <= 25)))
       set(s == 4 ? 6 : 5, 2, 1, 2, 1);
@@ -551,7 +560,7 @@ bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool 
     return false;
   if (aligned && rb >= 8192 && (rb > 16384 || (s > 1 && footprint < (64ull << 20)))) return false;
   const bool gather = k < 2 * c;
-  if (gather && contiguous && footprint < ((rb >= 16 ? 512u : 32u) << 10)) return false;
+  if (gather && footprint < ((rb >= 16 ? 512u : 32u) << 10)) return false;
   int lb;
   if (gather) {
     lb = s > 1 ? 14 : 12;
@@ -585,7 +594,8 @@ bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool 
 // tile and wavefront kernels.
 // align: the largest power of two (<= 16) dividing both data pointers.
 bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_config_t* cfg,
-                           size_t align, const DeviceInfo& d, bool have_device, Plan* p) {
+                           size_t align, bool contiguous, const DeviceInfo& d, bool have_device,
+                           Plan* p) {
   *p = Plan();
   if (rows == 0 || (mode == kModeInplace && k <= 1)) return BITREV_SUCCESS;
   const int forced_b = cfg ? cfg->tile_bits : 0;
@@ -598,7 +608,8 @@ bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_co
   const uint64_t footprint = row_bytes > UINT64_MAX / rows_u ? UINT64_MAX : row_bytes * rows_u;
   const int kind = mode == kModeInplace ? kKindInplace : kKindOutofplace;
   const PlanFields tp = table_plan(kind, s, 0, 0, footprint, d,
-                                   bytes_rule(kind, s, k, rows_u, footprint, 0, d));
+                                   bytes_rule(kind, s, k, rows_u, footprint, 0,
+                                              contiguous && align == 16, d));
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
                                          : (te.xcd_remap ? te.xcd_remap : (tp.xcd ? tp.xcd : 1));
@@ -665,20 +676,23 @@ bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_co
 bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, uint64_t src_pitch,
                            uint64_t dst_pitch, const bitrev_config_t* cfg, size_t align,
                            const DeviceInfo& d, bool have_device, Plan* p) {
-  const auto tiles = [&] { return plan_tiles(mode, k, s, rows, cfg, align, d, have_device, p); };
+  const uint64_t n = 1ull << k;
+  const bool contiguous = rows < 2 || (src_pitch == n && dst_pitch == n);
+  const auto tiles = [&] {
+    return plan_tiles(mode, k, s, rows, cfg, align, contiguous, d, have_device, p);
+  };
   if (rows < 2 || k > 16 || (mode == kModeInplace && k <= 1) || config_set(cfg)) return tiles();
   const TuneEntry te = tune_lookup(mode, s, k);
-  const uint64_t n = 1ull << k, footprint = (n * (uint64_t)s) * (uint64_t)rows;
+  const uint64_t footprint = (n * (uint64_t)s) * (uint64_t)rows;
   if (te.tile_bits || te.wg_per_cu || te.order || te.variant || te.xcd_remap || te.cache_hints ||
       (uint64_t)rows > (1ull << 62) >> k ||
       user_rows_apply(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, footprint, d))
     return tiles();
-  const bool contiguous = src_pitch == n && dst_pitch == n;
   const bool whole_lines = contiguous || ((src_pitch * s) % 64 == 0 && (dst_pitch * s) % 64 == 0);
   // the tile plan is made first only where it may be one linear tile per row
   *p = Plan();
   const uint64_t rb = n * (uint64_t)s;
-  const bool ask_tiles = k >= 8 && k % 2 == 0 &&
+  const bool ask_tiles = align == 16 && k >= 8 && k % 2 == 0 &&
                          (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20))));
   if (ask_tiles) {
     const bitrev_status_t st = tiles();
@@ -1136,7 +1150,8 @@ bitrev_status_t bitrev_dit_stages_ex(const void* src, void* dst, int log2n, int6
   if (st != BITREV_SUCCESS) return st;
   const int kind = inplace ? kKindDitInplace : kKindDitOutofplace;
   const uint64_t footprint = n * s * (uint64_t)rows;
-  const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages, d);
+  const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages,
+                                     true, d);
   const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d, rule);
   int b;
   if (cfg && cfg->tile_bits) {
@@ -1632,8 +1647,8 @@ bitrev_status_t bitrev_copy_tiled(const void* src, void* dst, int log2n, size_t 
   bitrev_status_t st = device_info(&d, false);
   if (st != BITREV_SUCCESS) return st;
   Plan p;
-  st = plan_tiles(kModeOutofplace, log2n, (int)elem_size, 1, cfg, pointer_align(src, dst), d, true,
-                  &p);
+  st = plan_tiles(kModeOutofplace, log2n, (int)elem_size, 1, cfg, pointer_align(src, dst), true, d,
+                  true, &p);
   if (st != BITREV_SUCCESS) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (p.path != BITREV_PATH_TILE) {

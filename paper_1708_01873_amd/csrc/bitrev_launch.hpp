@@ -138,6 +138,20 @@ hipError_t launch_dit_s16(int b, bool vec, const DitLaunch& a, hipStream_t st);
 int rows_block_threads(int s, int chunk_log2, bool gather);
 hipError_t launch_rows(int s, const RowsLaunch& a, hipStream_t st);
 
+// Short complex rows with up to three fused levels (k_rows_dit): chunks of
+// 2^kRowsDitLog2 bytes, 4 <= k < 8.
+constexpr int kRowsDitLog2 = 14;
+struct RowsDitLaunch {
+  const void* src;
+  void* dst;
+  int k;
+  uint64_t rows;
+  int stages, inverse;
+  int hints;
+  uint32_t grid;
+};
+hipError_t launch_rows_dit(int s, const RowsDitLaunch& a, hipStream_t st);
+
 // Scan of the tile work and the arrays that move whole (bitrev_batched.hip).
 hipError_t launch_batched_front(int s, const BatchedLaunch& a, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, uint32_t grid, int hints,

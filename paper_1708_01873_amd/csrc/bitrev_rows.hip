@@ -61,7 +61,36 @@ template <int S> hipError_t run_rows_hint(const RowsLaunch& a, hipStream_t st) {
   return run_rows_s<S, kThrough, kThrough>(a, st);
 }
 
+template <int S, int LV, int H, int LH>
+hipError_t run_rows_dit(const RowsDitLaunch& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_rows_dit<S, kRowsDitLog2, LV, H, LH>), dim3(a.grid),
+                     dim3(dit_rows_threads(kRowsDitLog2)), 0, st, a.src, a.dst, a.k, a.rows,
+                     a.inverse);
+  return hipGetLastError();
+}
+
+template <int S, int LV> hipError_t run_rows_dit_hint(const RowsDitLaunch& a, hipStream_t st) {
+  constexpr int kThrough = kHintStreamWriteThrough;
+  if (a.hints != kThrough) return run_rows_dit<S, LV, kHintPlain, kHintPlain>(a, st);
+  // plain loads for parts shorter than a 128-byte line, as in run_rows_hint
+  if (((uint64_t)S << a.k) < 8 * 128) return run_rows_dit<S, LV, kThrough, kHintPlain>(a, st);
+  return run_rows_dit<S, LV, kThrough, kThrough>(a, st);
+}
+
+template <int S> hipError_t run_rows_dit_levels(const RowsDitLaunch& a, hipStream_t st) {
+  switch (a.stages) {
+    case 1: return run_rows_dit_hint<S, 1>(a, st);
+    case 2: return run_rows_dit_hint<S, 2>(a, st);
+    case 3: return run_rows_dit_hint<S, 3>(a, st);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+hipError_t launch_rows_dit(int s, const RowsDitLaunch& a, hipStream_t st) {
+  return s == 8 ? run_rows_dit_levels<8>(a, st) : run_rows_dit_levels<16>(a, st);
+}
 
 int rows_block_threads(int s, int chunk_log2, bool gather) {
   return gather ? gather_threads(chunk_log2)

@@ -256,4 +256,73 @@ __global__ __launch_bounds__(gather_threads(LB)) void k_rows_gather(
   }
 }
 
+// Threads of a workgroup of k_rows_dit: eight 16-byte loads each.
+__host__ __device__ constexpr int dit_rows_threads(int lb) { return 1 << (lb - 7); }
+
+// The reversal of short complex rows fused with the first LV <= 3 levels: a
+// thread loads the vectors at one offset q of a row's eight parts, element (e,
+// q, j) of the index [e(3) | q | j]; the eight elements of one j go to the
+// contiguous block [rev(j) | rev(q)] of eight outputs, whole blocks of every
+// level, so the levels run in registers (dit_block_levels) and one pass
+// through LDS makes the writes linear, as in k_rows.
+// Bound by memory; the tile kernel's tiles are 2^(k / 2) elements wide (64
+// bytes a row at k = 6).  Kernel us, three arrays in turn: complex64 33 MiB
+// 2^4, two levels, 96 -> 14.0, 2^5 95 -> 12.6, 2^6, three levels, 29.7 -> 12.4,
+// 75 MiB of 2^7 65.6 -> 26.3; complex128 32 MiB 2^4 50.2 -> 11.9, 2^6 16.5 ->
+// 10.9 (a copy of 32 MiB: 10.7).
+template <int S, int LB, int LV, int H, int LH>
+__global__ __launch_bounds__(dit_rows_threads(LB)) void k_rows_dit(const void* src, void* dst, int k,
+                                                                  uint64_t rows, int inverse) {
+  typedef typename ComplexOf<S>::T F;
+  constexpr int C = vec_log2(S), CE = 1 << C, NT = dit_rows_threads(LB);
+  constexpr int VB = 8 / CE;  // vectors of a block
+  constexpr uint32_t CHV = 1u << (LB - 4);
+  __shared__ u32x4 lds[CHV];
+  const int w = k - 3 - C, lv = k - C;
+  const uint32_t vmask = (1u << lv) - 1u;
+  const uint32_t q = threadIdx.x & ((1u << w) - 1u), r = threadIdx.x >> w;
+  const F sg = inverse ? (F)-1 : (F)1;
+  const uint64_t step = (uint64_t)gridDim.x * (CHV >> lv);
+  for (uint64_t row0 = (uint64_t)blockIdx.x * (CHV >> lv); row0 < rows; row0 += step) {
+    const uint32_t live = rows - row0 < (CHV >> lv) ? (uint32_t)(rows - row0) : CHV >> lv;
+    const u32x4_a4* in = static_cast<const u32x4_a4*>(src) + (row0 << lv);
+    u32x4_a4* out = static_cast<u32x4_a4*>(dst) + (row0 << lv);
+    if (r < live) {
+      Chunk<S, 16> a[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e].v = ld_hint<LH>(in + (r << lv) + q + ((uint32_t)e << w));
+#pragma unroll
+      for (int j = 0; j < CE; ++j) {
+        F re[8], im[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          Cplx<F> x;
+          __builtin_memcpy(&x, &a[e].e[j], sizeof(x));
+          re[crev(e, 3)] = x.re;
+          im[crev(e, 3)] = x.im;
+        }
+        dit_block_levels<F, 8, LV>(re, im, sg);
+        const uint32_t o = (r << lv) + (rev_bits(q, w) + ((uint32_t)crev(j, C) << w)) * VB;
+#pragma unroll
+        for (int i = 0; i < VB; ++i) {
+          Chunk<S, 16> y;
+#pragma unroll
+          for (int c = 0; c < CE; ++c) {
+            const Cplx<F> x{re[i * CE + c], im[i * CE + c]};
+            __builtin_memcpy(&y.e[c], &x, sizeof(x));
+          }
+          lds[rows_slot(o + i)] = y.v;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t v = threadIdx.x + i * NT;
+      if ((v >> lv) < live) st_hint<H>(out + v, (u32x4_a4)lds[rows_slot(v)]);
+    }
+    __syncthreads();
+  }
+}
+
 }  // namespace bitrev

@@ -104,7 +104,7 @@ typedef enum bitrev_path {
   BITREV_PATH_NONE = 0,  /* nothing to do (in place with n <= 2, or no rows) */
   BITREV_PATH_WAVE = 1,  /* n <= 64: one wavefront per array, lane shuffles */
   BITREV_PATH_TILE = 2,  /* tiles of 2^b x 2^b staged through LDS */
-  BITREV_PATH_BATCHED = 3, /* persistent batched kernel (tiles + whole-array LDS) */
+  BITREV_PATH_BATCHED = 3, /* batched kernels (whole arrays in LDS, then tiles) */
   BITREV_PATH_ROWS = 4   /* two or more short rows: whole rows staged through LDS,
                           * work_items chunks of rows (no configuration forced) */
 } bitrev_path_t;
@@ -188,10 +188,11 @@ size_t bitrev_batched_workspace_size(int64_t num_arrays);
  *              holds after the call: [0] the number of arrays rejected,
  *              [1] the first rejected array (or -1) -- see
  *              bitrev_batched_errors()
- * Two kernels are enqueued: a one-workgroup prep kernel that checks every
+ * Two kernels are enqueued: one whose first workgroups check every
  * array (offsets[a+1] - offsets[a] == 2^log2n[a], 0 <= offsets[a],
  * offsets[a+1] <= data_elems, 0 <= log2n[a] <= BITREV_MAX_LOG2N) and scans
- * the per-array work counts into the workspace, then the persistent kernel.
+ * the per-array work counts into the workspace, and whose others move the
+ * short arrays, then the kernel for the tiles of the long ones.
  * A rejected array is left untouched; the others are still permuted.
  * Arrays must not overlap (the length check makes valid ones disjoint). */
 bitrev_status_t bitrev_batched(void* data, int64_t data_elems, const int64_t* offsets,

@@ -256,13 +256,22 @@ void merge_rows(const std::vector<PlanRow>& rows, int kind, int s, int d, int bm
 }
 
 
-// Whether a tuning file's plan rows decide anything for this launch.
+void load_env_tuning();
+
+// Whether a tuning file's plan rows, the kind's own or those it falls back to,
+// decide anything for this launch.
 bool user_rows_apply(int kind, int s, uint64_t footprint, const DeviceInfo& dev) {
-  PlanFields f;
+  load_env_tuning();
   std::lock_guard<std::mutex> lock(g_tune_mu);
   if (g_user_rows.empty()) return false;
-  merge_rows(g_user_rows, kind, s, 0, 0, footprint_class(footprint), dev, &f);
-  return f.b || f.wg || f.order || f.variant || f.xcd || f.hints;
+  const int c = footprint_class(footprint);
+  for (int k = kind; k >= 0; k = kKindParent[k])
+    for (const PlanRow& r : g_user_rows)  // whatever digit or tile width a row is for
+      if (r.kind == k && (!r.s || r.s == s) && (r.cmin < 0 || c >= r.cmin) &&
+          (r.cmax < 0 || c <= r.cmax) && (!r.cus || r.cus == dev.cus) &&
+          arch_matches(r.arch, dev.arch))
+        return true;
+  return false;
 }
 
 bitrev_status_t load_tuning_file(const char* path) {

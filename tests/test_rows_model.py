@@ -107,6 +107,14 @@ def test_a_tuning_file_still_decides(tmp_path):
         br.bitrev_load_tuning(str(f))
         assert br.bitrev_plan_query(7, 8, rows=100)["path"] == br.PATH_TILE
         assert br.bitrev_plan_query(7, 8, rows=100, mode=br.MODE_OUTOFPLACE)["path"] == br.PATH_ROWS
+        f.write_text("* 0 outofplace 8 0 5 -1 30 0 0 3 0 0 0\n")  # for one tile width only
+        br.bitrev_load_tuning(str(f))
+        assert br.bitrev_plan_query(7, 8, rows=100)["path"] == br.PATH_ROWS
+        assert br.bitrev_plan_query(7, 8, rows=100, mode=br.MODE_OUTOFPLACE)["path"] == br.PATH_TILE
+        p = br.bitrev_plan_query(16, 16, rows=64, mode=br.MODE_OUTOFPLACE)  # another size: the rule
+        assert p["order"] == 3
+        p = br.bitrev_plan_query(16, 8, rows=100, mode=br.MODE_OUTOFPLACE)  # the table and the row
+        assert (p["tile_bits"], p["variant"], p["order"]) == (5, 2, 3)
     finally:
         br.bitrev_load_tuning(None)
     assert br.bitrev_plan_query(5, 8, rows=100)["path"] == br.PATH_ROWS

@@ -25,7 +25,9 @@ def _log2_last(x: torch.Tensor) -> int:
 
 def _permute(x: torch.Tensor) -> torch.Tensor:
     k = _log2_last(x)
-    x = x.contiguous()
+    # the kernel reads memory: a conjugate or negative that torch keeps as a
+    # bit of the tensor (contiguous() keeps it too) is written out first
+    x = x.resolve_conj().resolve_neg().contiguous()
     y = torch.empty_like(x)
     if x.numel():
         src, size = _tensor_args(x, "src")

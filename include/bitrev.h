@@ -474,6 +474,14 @@ uint32_t bitrev_debug_digit_pair_at(int m, uint64_t w, int d);
 /* The w-th tile of the in-place digit kernels' order (grouped; the other
  * tile of its pair is its digit reversal). */
 uint32_t bitrev_debug_digit_inplace_pair_at(int m, uint64_t w, int d);
+/* What a batched call over num_arrays arrays in data_elems elements launches
+ * (bitrev_plan_query knows no batch): the tile kernel's width, grid, order and
+ * XCD mapping, the hints of the arrays that move whole, and in *whole_bits the
+ * log2 of the longest of those.  Without a device as bitrev_plan_query. */
+bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays,
+                                          size_t elem_size, int outofplace,
+                                          const bitrev_config_t* cfg, bitrev_plan_t* plan,
+                                          int* whole_bits);
 
 #ifdef __cplusplus
 }

@@ -108,6 +108,8 @@ _SIGNATURES = {
     "bitrev_debug_digit_pair_count": ([_I, _I], ctypes.c_uint64),
     "bitrev_debug_digit_inplace_pair_at": ([_I, ctypes.c_uint64, _I], ctypes.c_uint32),
     "bitrev_debug_digit_pair_at": ([_I, ctypes.c_uint64, _I], ctypes.c_uint32),
+    "bitrev_debug_batched_plan": ([_I64, _I64, _SZ, _I, _CFGP, ctypes.POINTER(Plan),
+                                   ctypes.POINTER(_I)], _I),
     "bitrev_transpose_inplace": ([_VP, _I, _SZ, _VP], _I),
     "bitrev_status_string": ([_I], ctypes.c_char_p),
     "bitrev_last_hip_error": ([], _I),

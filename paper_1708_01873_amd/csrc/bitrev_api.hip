@@ -347,15 +347,22 @@ TuneEntry tune_lookup(int mode, int s, int k) {
 
 // The table's plan for a launch of `kind` covering `footprint` bytes; bm is
 // the tile width in use (0 while it is being chosen), d the digit width.
-// Fields no row sets stay 0.  `f` starts with what is already decided.
+// Fields no row sets stay 0.  `f` starts with what is already decided; *file,
+// where given, gets the width, count and XCD mapping that a tuning file's rows set.
 PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const DeviceInfo& dev,
-                      PlanFields f = PlanFields()) {
+                      PlanFields f = PlanFields(), PlanFields* file = nullptr) {
   load_env_tuning();
   const int c = footprint_class(footprint);
   const std::vector<PlanRow>& builtin = builtin_rows();
   std::lock_guard<std::mutex> lock(g_tune_mu);
   for (int k = kind; k >= 0; k = kKindParent[k]) {
+    const PlanFields before = f;
     merge_rows(g_user_rows, k, s, d, bm, c, dev, &f);
+    if (file) {
+      if (!before.b) file->b = f.b;
+      if (!before.wg) file->wg = f.wg;
+      if (!before.xcd) file->xcd = f.xcd;
+    }
     merge_rows(builtin, k, s, d, bm, c, dev, &f);
   }
   return f;
@@ -747,12 +754,14 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   p->b = b;
   // order, XCD mapping and workgroups per CU for the width in use (the
   // table's per-CU counts belong to the widths they were measured at)
-  const PlanFields tp = table_plan(kind, s, 0, b, 0, d);
+  PlanFields file;
+  const PlanFields tp = table_plan(kind, s, 0, b, 0, d, PlanFields(), &file);
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
                                          : (te.xcd_remap ? te.xcd_remap : (tp.xcd ? tp.xcd : 1));
-  p->persistent =
-      (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || user_rows_apply(kind, s, 0, d);
+  // (a file that leaves the count open leaves the library its own grid: one
+  // tile per workgroup, which the tuner timed such a row with)
+  p->persistent = (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || file.wg > 0;
   p->threads = threads_of(s, b, true);
   p->lds = tile_lds_bytes_for(s, b, 2);
   int per_cu = te.wg_per_cu > 0 ? te.wg_per_cu : tp.wg;
@@ -1449,6 +1458,37 @@ static bitrev_status_t check_batched_args(const void* src, void* data, int64_t d
   return BITREV_SUCCESS;
 }
 
+// What a batched launch takes from the plan and from the batch: a->num and
+// a->data_elems are set, the geometry is filled in.
+static void batched_geometry(const Plan& p, const bitrev_config_t* cfg, size_t elem_size,
+                             const DeviceInfo& d, BatchedLaunch* a) {
+  a->b = p.b;
+  // Arrays that move whole through LDS: those too short for a tile and, no
+  // width forced, all up to 16 KiB (5000 complex128 arrays of 2^10 35.8 ->
+  // 28.8 us), in batches of short arrays (under 16 KiB on average) up to 32 KiB
+  // (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500 complex128 arrays
+  // of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
+  a->whole = 2 * p.b - 1;
+  const bool shorts = (uint64_t)a->data_elems / (uint64_t)a->num < 16384 / elem_size;
+  if (!(cfg && cfg->tile_bits))
+    while ((elem_size << (a->whole + 1)) <= (shorts ? 32768u : 16384u)) ++a->whole;
+  a->hints =
+      (uint64_t)a->data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
+  a->balanced = order_code(p.order);
+  // one item per workgroup runs in dispatch order: contiguous XCD ranges walk
+  // eight distant regions at once (4096 complex64 arrays: +10%)
+  const bool ranges = p.xcd_remap != 2 && (p.persistent || (cfg && cfg->xcd_remap));
+  a->xcds = ranges ? d.xcds : 1;
+  a->grid = p.grid;
+  if (!p.persistent) {
+    // no more workgroups than the data hold tiles: those without an item
+    // cost 1 us per thousand (in short batches few arrays have tiles)
+    uint64_t most = ((uint64_t)a->data_elems >> (2 * p.b)) + 1;
+    if (shorts) most = most / 2 > 2u * (uint32_t)d.cus ? most / 2 : 2u * (uint32_t)d.cus;
+    if (most < a->grid) a->grid = round_up(most, (uint32_t)d.xcds);
+  }
+}
+
 static bitrev_status_t run_batched(const void* src, void* data, int64_t data_elems,
                                    const int64_t* offsets, const int32_t* log2n,
                                    int64_t num_arrays, size_t elem_size, void* workspace,
@@ -1477,30 +1517,7 @@ static bitrev_status_t run_batched(const void* src, void* data, int64_t data_ele
   a.num = num_arrays;
   a.data_elems = data_elems;
   a.ws = static_cast<int64_t*>(workspace);
-  a.b = p.b;
-  // Arrays that move whole through LDS: those too short for a tile and, no
-  // width forced, all up to 16 KiB (5000 complex128 arrays of 2^10 35.8 ->
-  // 28.8 us), in batches of short arrays (under 16 KiB on average) up to 32 KiB
-  // (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500 complex128 arrays
-  // of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
-  a.whole = 2 * p.b - 1;
-  const bool shorts = (uint64_t)data_elems / (uint64_t)num_arrays < 16384 / elem_size;
-  if (!(cfg && cfg->tile_bits))
-    while ((elem_size << (a.whole + 1)) <= (shorts ? 32768u : 16384u)) ++a.whole;
-  a.hints = (uint64_t)data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
-  a.balanced = order_code(p.order);
-  // one item per workgroup runs in dispatch order: contiguous XCD ranges walk
-  // eight distant regions at once (4096 complex64 arrays: +10%)
-  const bool ranges = p.xcd_remap != 2 && (p.persistent || (cfg && cfg->xcd_remap));
-  a.xcds = ranges ? d.xcds : 1;
-  a.grid = p.grid;
-  if (!p.persistent) {
-    // no more workgroups than the data hold tiles: those without an item
-    // cost 1 us per thousand (in short batches few arrays have tiles)
-    uint64_t most = ((uint64_t)data_elems >> (2 * p.b)) + 1;
-    if (shorts) most = most / 2 > 2u * (uint32_t)d.cus ? most / 2 : 2u * (uint32_t)d.cus;
-    if (most < a.grid) a.grid = round_up(most, (uint32_t)d.xcds);
-  }
+  batched_geometry(p, cfg, elem_size, d, &a);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   hipError_t e = launch_batched_front((int)elem_size, a, hs);
   if (e != hipSuccess) return hip_fail(e);
@@ -1636,6 +1653,38 @@ bitrev_status_t bitrev_plan_query(int log2n, size_t elem_size, int64_t rows, int
       (p.path == BITREV_PATH_TILE || p.path == BITREV_PATH_ROWS) ? p.hints + 1 : 0;
   plan->work_items = p.total;
   plan->lds_bytes = p.lds;
+  return BITREV_SUCCESS;
+}
+
+bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays,
+                                          size_t elem_size, int outofplace,
+                                          const bitrev_config_t* cfg, bitrev_plan_t* plan,
+                                          int* whole_bits) {
+  if (plan == NULL || whole_bits == NULL || data_elems < 0 || num_arrays < 1 ||
+      num_arrays > (1ll << 40) || !valid_elem_size(elem_size) || !valid_config(cfg))
+    return BITREV_ERROR_INVALID_VALUE;
+  DeviceInfo d;
+  bool have_device = false;
+  bitrev_status_t st = device_info(&d, true, &have_device);
+  if (st != BITREV_SUCCESS) return st;
+  Plan p;
+  st = plan_batched((int)elem_size, cfg, d, have_device, outofplace != 0, &p);
+  if (st != BITREV_SUCCESS) return st;
+  BatchedLaunch a = {};
+  a.num = num_arrays;
+  a.data_elems = data_elems;
+  batched_geometry(p, cfg, elem_size, d, &a);
+  memset(plan, 0, sizeof *plan);
+  plan->path = p.path;
+  plan->tile_bits = a.b;
+  plan->block_threads = p.threads;
+  plan->grid_blocks = (int)a.grid;
+  plan->order = p.order;
+  plan->vector_access = 1;
+  plan->xcd_remap = a.xcds > 1 ? 1 : 2;
+  plan->cache_hints = a.hints + 1;
+  plan->lds_bytes = p.lds;
+  *whole_bits = a.whole;
   return BITREV_SUCCESS;
 }
 

@@ -536,6 +536,7 @@ struct Plan {
   uint64_t total = 0;
   size_t lds = 0;
   bool persistent = false; // batched: the caller or a tuning file set the grid
+  bool forced_width = false;  // batched: ... set the tile width
   int chunk_log2 = 0;      // whole-row path: bytes per workgroup
   bool gather = false;
 };
@@ -743,7 +744,9 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   *p = Plan();
   const TuneEntry te = tune_lookup(kModeBatched, s, -1);
   const int kind = oop ? kKindBatchedOop : kKindBatched;
-  const PlanFields t1 = table_plan(kind, s, 0, 0, 0, d);
+  PlanFields file;
+  const PlanFields t1 = table_plan(kind, s, 0, 0, 0, d, PlanFields(), &file);
+  p->forced_width = (cfg && cfg->tile_bits) || te.tile_bits || file.b;
   int b = (cfg && cfg->tile_bits) ? cfg->tile_bits
                                   : (te.tile_bits ? te.tile_bits : (t1.b ? t1.b : max_tile_bits(s)));
   if (!(cfg && cfg->tile_bits) && b > max_tile_bits(s)) b = max_tile_bits(s);
@@ -754,7 +757,6 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   p->b = b;
   // order, XCD mapping and workgroups per CU for the width in use (the
   // table's per-CU counts belong to the widths they were measured at)
-  PlanFields file;
   const PlanFields tp = table_plan(kind, s, 0, b, 0, d, PlanFields(), &file);
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
@@ -1463,14 +1465,15 @@ static bitrev_status_t check_batched_args(const void* src, void* data, int64_t d
 static void batched_geometry(const Plan& p, const bitrev_config_t* cfg, size_t elem_size,
                              const DeviceInfo& d, BatchedLaunch* a) {
   a->b = p.b;
-  // Arrays that move whole through LDS: those too short for a tile and, no
-  // width forced, all up to 16 KiB (5000 complex128 arrays of 2^10 35.8 ->
+  // Arrays that move whole through LDS: those too short for a tile and, where
+  // neither the caller nor a tuning file sets the width (a tuned width is timed
+  // as a forced one), all up to 16 KiB (5000 complex128 arrays of 2^10 35.8 ->
   // 28.8 us), in batches of short arrays (under 16 KiB on average) up to 32 KiB
   // (20000 complex64 arrays of 2^0-2^12: 69 -> 51 us; 1500 complex128 arrays
   // of 2^8-2^14, 75 KiB on average, would lose 47 -> 52)
   a->whole = 2 * p.b - 1;
   const bool shorts = (uint64_t)a->data_elems / (uint64_t)a->num < 16384 / elem_size;
-  if (!(cfg && cfg->tile_bits))
+  if (!p.forced_width)
     while ((elem_size << (a->whole + 1)) <= (shorts ? 32768u : 16384u)) ++a->whole;
   a->hints =
       (uint64_t)a->data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;

@@ -186,8 +186,10 @@ def tune_plain(log2n: int, elem_size: int, mode: int = MODE_INPLACE, *, rows: in
 def tune_batched(data, offsets, log2n, *, reps: int = 6, wg_per_cu=(0, 1, 2, 4, 8),
                  tile_bits=None, orders=(1, 2, 3), xcd_remaps=(1, 2)) -> TuneResult:
     """Time the batched launch on the caller's own batch (device tensors as
-    for bitrev_batched) over tile widths, orders and workgroups per CU.  Each
-    candidate runs an even number of times, so `data` ends unchanged."""
+    for bitrev_batched) over tile widths, orders and workgroups per CU; width 0
+    is the built-in width with the library's own split of whole arrays and
+    tiles, and stays open in the row.  Each candidate runs an even number of
+    times, so `data` ends unchanged."""
     s = data.element_size()
     num = log2n.numel()
     ws = torch.empty(max(1, bitrev_batched_workspace_size(num)), dtype=torch.uint8,
@@ -195,7 +197,7 @@ def tune_batched(data, offsets, log2n, *, reps: int = 6, wg_per_cu=(0, 1, 2, 4, 
     cus = torch.cuda.get_device_properties(data.device).multi_processor_count
     clock = _Clock(data.device, 0)
     reps = _even(reps)
-    bs = tile_bits or [b for b in range(2, MAX_TILE_BITS[s] + 1) if (s << b) >= 16]
+    bs = tile_bits or [0] + [b for b in range(2, MAX_TILE_BITS[s] + 1) if (s << b) >= 16]
     ranking = []
     for b in bs:
         for order in orders:

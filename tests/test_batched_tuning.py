@@ -50,3 +50,54 @@ def test_a_row_without_a_count_keeps_the_grid_by_tiles(tuned, elems, num, s, oop
     assert launch(elems, num, s, oop) == dict(base, order=3, grid_blocks=2 * CUS, xcd_remap=1)
     tuned("batched %d -1 0 2 3 0 1" % s)
     assert launch(elems, num, s, oop) == dict(base, order=3, grid_blocks=2 * CUS, xcd_remap=1)
+
+
+@pytest.mark.parametrize("wg", (0, 4))
+@pytest.mark.parametrize("s", (1, 2, 4, 8, 16))
+@pytest.mark.parametrize("elems,num", BATCHES)
+def test_a_width_is_the_same_launch_from_every_source(tuned, elems, num, s, wg):
+    """A forced tile width, an exact entry and a plan row of it: the same
+    arrays move whole, so a row launches what the tuner timed it with; without
+    a width (0) the row keeps the library's split."""
+    for b in range(0 if wg else 1, {1: 7, 2: 7, 4: 7, 8: 6, 16: 6}[s] + 1):
+        if b == 1 or 0 < (s << b) < 16:
+            continue
+        for order, xcd in ((1, 1), (3, 2)):
+            br.bitrev_load_tuning(None)
+            want = launch(elems, num, s, tile_bits=b, order=order, grid_blocks=wg * CUS,
+                          xcd_remap=xcd)
+            tuned("* 0 batched %d 0 0 -1 -1   %d %d %d 0 %d 0" % (s, b, wg, order, xcd))
+            got = launch(elems, num, s)
+            if wg:  # (the mapping of the library's own grid: the next test)
+                assert got == want, (b, order, xcd)
+            else:
+                assert dict(got, xcd_remap=0) == dict(want, xcd_remap=0), (b, order, xcd)
+            tuned("batched %d -1 %d %d %d 0 %d" % (s, b, wg, order, xcd))
+            got = launch(elems, num, s)
+            assert dict(got, xcd_remap=0) == dict(want, xcd_remap=0), (b, order, xcd)
+
+
+def test_the_tuner_also_times_the_built_in_width(monkeypatch):
+    """Its candidates include the call without a forced width, whose row
+    leaves the width open."""
+    from paper_1708_01873_amd import tune
+    import torch
+
+    class Clock:
+        def __init__(self, *a):
+            pass
+
+        def median_ms(self, fn, reps):
+            fn()
+            return 1.0
+    seen = []
+    monkeypatch.setattr(tune, "_Clock", Clock)
+    monkeypatch.setattr(tune, "bitrev_batched", lambda *a, **cfg: seen.append(cfg))
+    monkeypatch.setattr(torch.cuda, "get_device_properties",
+                        lambda d: type("P", (), {"multi_processor_count": CUS}))
+    data, log2n = torch.zeros(16, dtype=torch.complex64), torch.zeros(16, dtype=torch.int32)
+    r = tune.tune_batched(data, torch.arange(17), log2n, wg_per_cu=(0, 2))
+    widths = {c["tile_bits"] for c in seen if c}
+    assert widths == {0, 2, 3, 4, 5, 6}
+    assert {c.tile_bits for c in r.ranking} == widths
+    assert tune.result_row(r, "gfx950", CUS).split()[8] == "0"  # all equal: the first

@@ -119,8 +119,9 @@ typedef struct bitrev_plan {
   int vector_access;    /* 1: 16-byte global accesses; 0: one element per access */
   int variant;          /* 1 one item per workgroup, 2 persistent pipelined, 3 register-staged */
   int xcd_remap;        /* 1 contiguous ranges per XCD, 2 dispatch order (batched:
-                         * of a grid that the caller or a tuning file sets; the
-                         * library's own runs in dispatch order) */
+                         * where the caller or a tuning file sets the mapping or
+                         * the grid; otherwise the library's own grid runs in
+                         * dispatch order -- bitrev_debug_batched_plan tells) */
   int cache_hints;      /* 1 plain, 2 streaming loads, 3 streaming stores,
                          * 4 streaming loads and write-through stores */
   uint64_t work_items;  /* tile pairs (in place) or tiles (out of place), all rows */

@@ -537,6 +537,7 @@ struct Plan {
   size_t lds = 0;
   bool persistent = false; // batched: the caller or a tuning file set the grid
   bool forced_width = false;  // batched: ... set the tile width
+  bool forced_xcd = false;    // batched: ... set the XCD mapping
   int chunk_log2 = 0;      // whole-row path: bytes per workgroup
   bool gather = false;
 };
@@ -764,6 +765,7 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   // (a file that leaves the count open leaves the library its own grid: one
   // tile per workgroup, which the tuner timed such a row with)
   p->persistent = (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || file.wg > 0;
+  p->forced_xcd = (cfg && cfg->xcd_remap) || te.xcd_remap || file.xcd;
   p->threads = threads_of(s, b, true);
   p->lds = tile_lds_bytes_for(s, b, 2);
   int per_cu = te.wg_per_cu > 0 ? te.wg_per_cu : tp.wg;
@@ -1462,8 +1464,8 @@ static bitrev_status_t check_batched_args(const void* src, void* data, int64_t d
 
 // What a batched launch takes from the plan and from the batch: a->num and
 // a->data_elems are set, the geometry is filled in.
-static void batched_geometry(const Plan& p, const bitrev_config_t* cfg, size_t elem_size,
-                             const DeviceInfo& d, BatchedLaunch* a) {
+static void batched_geometry(const Plan& p, size_t elem_size, const DeviceInfo& d,
+                             BatchedLaunch* a) {
   a->b = p.b;
   // Arrays that move whole through LDS: those too short for a tile and, where
   // neither the caller nor a tuning file sets the width (a tuned width is timed
@@ -1478,9 +1480,10 @@ static void batched_geometry(const Plan& p, const bitrev_config_t* cfg, size_t e
   a->hints =
       (uint64_t)a->data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
   a->balanced = order_code(p.order);
-  // one item per workgroup runs in dispatch order: contiguous XCD ranges walk
-  // eight distant regions at once (4096 complex64 arrays: +10%)
-  const bool ranges = p.xcd_remap != 2 && (p.persistent || (cfg && cfg->xcd_remap));
+  // one item per workgroup runs in dispatch order unless the caller or a tuning
+  // file asks otherwise: contiguous XCD ranges walk eight distant regions at
+  // once (4096 complex64 arrays: +10%)
+  const bool ranges = p.xcd_remap != 2 && (p.persistent || p.forced_xcd);
   a->xcds = ranges ? d.xcds : 1;
   a->grid = p.grid;
   if (!p.persistent) {
@@ -1520,7 +1523,7 @@ static bitrev_status_t run_batched(const void* src, void* data, int64_t data_ele
   a.num = num_arrays;
   a.data_elems = data_elems;
   a.ws = static_cast<int64_t*>(workspace);
-  batched_geometry(p, cfg, elem_size, d, &a);
+  batched_geometry(p, elem_size, d, &a);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   hipError_t e = launch_batched_front((int)elem_size, a, hs);
   if (e != hipSuccess) return hip_fail(e);
@@ -1676,7 +1679,7 @@ bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays
   BatchedLaunch a = {};
   a.num = num_arrays;
   a.data_elems = data_elems;
-  batched_geometry(p, cfg, elem_size, d, &a);
+  batched_geometry(p, elem_size, d, &a);
   memset(plan, 0, sizeof *plan);
   plan->path = p.path;
   plan->tile_bits = a.b;

@@ -101,3 +101,21 @@ def test_the_tuner_also_times_the_built_in_width(monkeypatch):
     assert widths == {0, 2, 3, 4, 5, 6}
     assert {c.tile_bits for c in r.ranking} == widths
     assert tune.result_row(r, "gfx950", CUS).split()[8] == "0"  # all equal: the first
+
+
+@pytest.mark.parametrize("xcd", (1, 2))
+@pytest.mark.parametrize("s", (1, 2, 4, 8, 16))
+@pytest.mark.parametrize("elems,num", BATCHES)
+def test_a_mapping_is_honoured_from_every_source(tuned, elems, num, s, xcd):
+    """Contiguous XCD ranges or dispatch order, asked for by the caller, an
+    exact entry or a plan row, with and without a width and a count; where
+    nobody asks, the library's own grid runs in dispatch order."""
+    assert launch(elems, num, s)["xcd_remap"] == 2
+    for b, wg in ((0, 0), (5, 0), (0, 2)):
+        br.bitrev_load_tuning(None)
+        want = launch(elems, num, s, tile_bits=b, order=2, grid_blocks=wg * CUS, xcd_remap=xcd)
+        assert want["xcd_remap"] == xcd
+        tuned("batched %d -1 %d %d 2 0 %d" % (s, b, wg, xcd))
+        assert launch(elems, num, s) == want, (b, wg)
+        tuned("* 0 batched %d 0 0 -1 -1   %d %d 2 0 %d 0" % (s, b, wg, xcd))
+        assert launch(elems, num, s) == want, (b, wg)

@@ -483,6 +483,12 @@ bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays
                                           size_t elem_size, int outofplace,
                                           const bitrev_config_t* cfg, bitrev_plan_t* plan,
                                           int* whole_bits);
+/* The plan of a call with fused levels (stages >= 1) on arrays aligned to
+ * `align` bytes (16, or 8 for complex64): BITREV_PATH_ROWS, or tiles with the
+ * variants of bitrev_dit_stages_ex. */
+bitrev_status_t bitrev_debug_dit_plan(int log2n, int64_t rows, int stages, int outofplace,
+                                      int dtype, size_t align, const bitrev_config_t* cfg,
+                                      bitrev_plan_t* plan);
 
 #ifdef __cplusplus
 }

@@ -110,6 +110,7 @@ _SIGNATURES = {
     "bitrev_debug_digit_pair_at": ([_I, ctypes.c_uint64, _I], ctypes.c_uint32),
     "bitrev_debug_batched_plan": ([_I64, _I64, _SZ, _I, _CFGP, ctypes.POINTER(Plan),
                                    ctypes.POINTER(_I)], _I),
+    "bitrev_debug_dit_plan": ([_I, _I64, _I, _I, _I, _SZ, _CFGP, ctypes.POINTER(Plan)], _I),
     "bitrev_transpose_inplace": ([_VP, _I, _SZ, _VP], _I),
     "bitrev_status_string": ([_I], ctypes.c_char_p),
     "bitrev_last_hip_error": ([], _I),

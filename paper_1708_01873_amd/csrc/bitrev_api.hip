@@ -403,10 +403,19 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //    L2s still hold there (2^22 15.0 -> 12.4, from cold caches 18.3 -> 18.2).
 //    Fewer gain 1 to 8% so and lose up to 14% from cold caches (one level 15.5
 //    -> 18.0): left to the table.
+//  - Up to four complex128 levels in place at 4 to 64 MiB, where the table's
+//    in-place rows give two tiles at b = 4: the register-staged pair at b = 5
+//    stays for rows of 2^10 and 2^11, where b = 5 is one tile or two a row
+//    (2^10 15 MiB, four levels 6.8 -> 5.6, 2^11 12 MiB 6.0 -> 5.0), for two
+//    levels (2^12 15 MiB 6.3 -> 5.7, 2^19 4.7 -> 4.4; against it 2^13 23 MiB
+//    8.2 -> 9.7, 2^20 7.0 -> 7.6), and for rows of 2^14 from 16 MiB (30 MiB,
+//    four levels 11.2 -> 10.5).  Elsewhere it loses (one level: 2^13 23 MiB
+//    8.2 -> 10.2, 2^16 15 MiB 5.8 -> 7.3, one array of 2^21 12.1 -> 13.8) or
+//    is level from cold caches (2^12 15 MiB, four levels 6.7 -> 6.1, 10.2).
 PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint, int stages,
                       bool linear, const DeviceInfo& dev) {
   PlanFields f;
-  if (kind == kKindDitInplace || dev.cus != 256 || !arch_matches("gfx950", dev.arch)) return f;
+  if (dev.cus != 256 || !arch_matches("gfx950", dev.arch)) return f;
   auto set = [&f](int b, int variant, int order, int xcd, int hints) {
     f.b = b;
     f.variant = variant;
@@ -417,7 +426,11 @@ PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint,
   const uint64_t mib = 1ull << 20, row = (uint64_t)s << k;
   const bool many = rows >= 2 && row >= mib / 4 && row <= 8 * mib;
   const int c = footprint_class(footprint);
-  if (stages == 0 && !linear) {
+  if (kind == kKindDitInplace) {
+    if (s == 16 && stages <= 4 && c >= 22 && c <= 25 && k >= 10 &&
+        (k <= 11 || stages == 2 || (k == 14 && c >= 24)))
+      set(5, 3, 2, 2, 4);
+  } else if (stages == 0 && !linear) {
     if (kind == kKindInplace && c <= 25 && s != 1) set(s == 2 ? 7 : s == 4 ? 6 : 5, 2, 1, 2, 1);
     if (kind == kKindOutofplace && s == 2 && c <= 24) set(7, 2, 2, 2, 1);
     if (kind == kKindOutofplace && s == 16 && c <= 24) set(5, 2, 2, 2, 1);
@@ -1145,6 +1158,100 @@ static bool rows_dit_applies(int k, uint64_t rows, const bitrev_config_t* cfg) {
   return rows >= 2 && !config_set(cfg) && k >= 4 && k < 8;
 }
 
+// How a call with fused levels runs: whole rows in LDS, or tiles of width b.
+// The pointers and the direction are the caller's to fill in.
+struct DitPlan {
+  bool whole_rows = false;
+  RowsDitLaunch r = {};
+  DitLaunch a = {};
+  int b = 0;
+  bool vec = true;
+  int order = 0, xcd_remap = 0;
+};
+
+static bitrev_status_t plan_dit(bool inplace, int log2n, int64_t rows, int stages, size_t s,
+                                const bitrev_config_t* cfg, size_t align, const DeviceInfo& d,
+                                DitPlan* p) {
+  const uint64_t n = 1ull << log2n;
+  const int kind = inplace ? kKindDitInplace : kKindDitOutofplace;
+  const uint64_t footprint = n * s * (uint64_t)rows;
+  if (rows_dit_applies(log2n, (uint64_t)rows, cfg) &&
+      !user_rows_apply(kind, (int)s, footprint, d)) {
+    RowsDitLaunch& r = p->r;
+    p->whole_rows = true;
+    r.k = log2n;
+    r.rows = (uint64_t)rows;
+    r.stages = stages;
+    r.hints = footprint >= (64ull << 20) && align == 16 ? kHintStreamWriteThrough : kHintPlain;
+    const uint64_t per = (1ull << kRowsDitLog2) / (n * s);
+    const uint64_t chunks = ((uint64_t)rows + per - 1) / per;
+    r.grid = (uint32_t)(chunks < (1u << 20) ? chunks : (1u << 20));
+    return BITREV_SUCCESS;
+  }
+  const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages,
+                                     true, d);
+  const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d, rule);
+  int b;
+  if (cfg && cfg->tile_bits) {
+    b = cfg->tile_bits;  // forced: must hold the levels and fit (a
+                         // rectangular tile needs only b + (b - 1) or
+                         // b + (b - 2) bits, checked below)
+    const bool rect = cfg->variant >= 2;
+    if ((2 * b > log2n && !rect) || b > max_tile_bits((int)s)) return BITREV_ERROR_NOT_SUPPORTED;
+  } else {
+    b = t1.b ? t1.b : max_tile_bits((int)s);
+    if (b < stages) b = stages;
+    if (b > max_tile_bits((int)s)) b = max_tile_bits((int)s);
+    if (2 * b > log2n) b = log2n / 2;
+  }
+  const size_t lds = tile_lds_bytes_for((int)s, b, 2) + ((size_t)1 << b) * (s / 2);
+  if (b < stages || lds > d.lds_per_block) return BITREV_ERROR_NOT_SUPPORTED;
+  // square tiles (a forced rectangular plan with 2b > log2n gets its own
+  // geometry below or is rejected there)
+  const int m = 2 * b <= log2n ? log2n - 2 * b : 0;
+  if (m > 32) return BITREV_ERROR_NOT_SUPPORTED;
+  DitLaunch& a = p->a;
+  a.t.m = m;
+  a.t.items_per_seg = inplace ? pair_count(m) : (1ull << m);
+  a.t.total_items = a.t.items_per_seg * (uint64_t)rows;
+  a.t.seg_elems = n;
+  const PlanFields tp = table_plan(kind, (int)s, 0, b, footprint, d, rule);
+  // rectangular tiles out of place (variant 2: source rows of 2^(b-1)
+  // elements, 3: of 2^(b-2); b = 5 or 6, 16-byte aligned arrays)
+  const int dvar = (cfg && cfg->variant) ? cfg->variant : (tp.variant ? tp.variant : 1);
+  if (inplace && dvar == 3 && 2 * b <= log2n) {
+    // in place: the pair in registers, each tile staged in turn through one
+    // LDS tile
+    a.rs = 1;
+  } else if (dvar >= 2) {
+    const int bz = b - (dvar - 1);
+    const bool fits = !inplace && (b == 5 || b == 6) && align % 16 == 0 &&
+                      log2n >= b + bz && log2n - b - bz <= 32;
+    if (fits) {
+      a.rect_bz = bz;
+      a.t.m = log2n - b - bz;
+      a.t.items_per_seg = 1ull << a.t.m;
+      a.t.total_items = a.t.items_per_seg * (uint64_t)rows;
+    } else if (cfg && cfg->variant) {
+      return BITREV_ERROR_NOT_SUPPORTED;
+    }
+  }
+  p->order = (cfg && cfg->order) ? cfg->order : (tp.order ? tp.order : 2);
+  a.t.balanced = order_code(p->order);
+  p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap : (tp.xcd ? tp.xcd : 1);
+  a.t.xcds = p->xcd_remap == 2 ? 1 : d.xcds;
+  a.t.grid = (cfg && cfg->grid_blocks > 0) ? round_up((uint64_t)cfg->grid_blocks, (uint32_t)d.xcds)
+                                           : default_grid(a.t.total_items, d);
+  a.t.pipelined = 0;
+  a.t.hints = (cfg && cfg->cache_hints) ? cfg->cache_hints - 1
+                                        : (tp.hints ? tp.hints - 1 : kHintPlain);
+  a.stages = stages;
+  const size_t vb = (s << b) < 16 ? (s << b) : 16;
+  p->b = b;
+  p->vec = align % vb == 0;
+  return BITREV_SUCCESS;
+}
+
 bitrev_status_t bitrev_dit_stages_ex(const void* src, void* dst, int log2n, int64_t rows,
                                      int stages, int inverse, int dtype,
                                      const bitrev_config_t* cfg, void* stream) {
@@ -1178,89 +1285,22 @@ bitrev_status_t bitrev_dit_stages_ex(const void* src, void* dst, int log2n, int6
   DeviceInfo d;
   bitrev_status_t st = device_info(&d, false);
   if (st != BITREV_SUCCESS) return st;
-  const int kind = inplace ? kKindDitInplace : kKindDitOutofplace;
-  const uint64_t footprint = n * s * (uint64_t)rows;
-  if (rows_dit_applies(log2n, (uint64_t)rows, cfg) &&
-      !user_rows_apply(kind, (int)s, footprint, d)) {
-    RowsDitLaunch r;
-    r.src = src;
-    r.dst = dst;
-    r.k = log2n;
-    r.rows = (uint64_t)rows;
-    r.stages = stages;
-    r.inverse = inverse;
-    r.hints = footprint >= (64ull << 20) && pointer_align(src, dst) == 16 ? kHintStreamWriteThrough
-                                                                         : kHintPlain;
-    const uint64_t per = (1ull << kRowsDitLog2) / (n * s);
-    const uint64_t chunks = ((uint64_t)rows + per - 1) / per;
-    r.grid = (uint32_t)(chunks < (1u << 20) ? chunks : (1u << 20));
-    const hipError_t e = launch_rows_dit((int)s, r, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? BITREV_SUCCESS : hip_fail(e);
-  }
-  const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages,
-                                     true, d);
-  const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d, rule);
-  int b;
-  if (cfg && cfg->tile_bits) {
-    b = cfg->tile_bits;  // forced: must hold the levels and fit (a
-                         // rectangular tile needs only b + (b - 1) or
-                         // b + (b - 2) bits, checked below)
-    const bool rect = cfg->variant >= 2;
-    if ((2 * b > log2n && !rect) || b > max_tile_bits((int)s)) return BITREV_ERROR_NOT_SUPPORTED;
+  DitPlan p;
+  st = plan_dit(inplace, log2n, rows, stages, s, cfg, pointer_align(src, dst), d, &p);
+  if (st != BITREV_SUCCESS) return st;
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  hipError_t e;
+  if (p.whole_rows) {
+    p.r.src = src;
+    p.r.dst = dst;
+    p.r.inverse = inverse;
+    e = launch_rows_dit((int)s, p.r, hs);
   } else {
-    b = t1.b ? t1.b : max_tile_bits((int)s);
-    if (b < stages) b = stages;
-    if (b > max_tile_bits((int)s)) b = max_tile_bits((int)s);
-    if (2 * b > log2n) b = log2n / 2;
+    p.a.t.src = src;
+    p.a.t.dst = dst;
+    p.a.inverse = inverse;
+    e = s == 8 ? launch_dit_s8(p.b, p.vec, p.a, hs) : launch_dit_s16(p.b, p.vec, p.a, hs);
   }
-  const size_t lds = tile_lds_bytes_for((int)s, b, 2) + ((size_t)1 << b) * (s / 2);
-  if (b < stages || lds > d.lds_per_block) return BITREV_ERROR_NOT_SUPPORTED;
-  // square tiles (a forced rectangular plan with 2b > log2n gets its own
-  // geometry below or is rejected there)
-  const int m = 2 * b <= log2n ? log2n - 2 * b : 0;
-  if (m > 32) return BITREV_ERROR_NOT_SUPPORTED;
-  DitLaunch a;
-  a.t.src = src;
-  a.t.dst = dst;
-  a.t.m = m;
-  a.t.items_per_seg = inplace ? pair_count(m) : (1ull << m);
-  a.t.total_items = a.t.items_per_seg * (uint64_t)rows;
-  a.t.seg_elems = n;
-  const PlanFields tp = table_plan(kind, (int)s, 0, b, footprint, d, rule);
-  // rectangular tiles out of place (variant 2: source rows of 2^(b-1)
-  // elements, 3: of 2^(b-2); b = 5 or 6, 16-byte aligned arrays)
-  const int dvar = (cfg && cfg->variant) ? cfg->variant : (tp.variant ? tp.variant : 1);
-  if (inplace && dvar == 3 && 2 * b <= log2n) {
-    // in place: the pair in registers, each tile staged in turn through one
-    // LDS tile
-    a.rs = 1;
-  } else if (dvar >= 2) {
-    const int bz = b - (dvar - 1);
-    const bool fits = !inplace && (b == 5 || b == 6) && pointer_align(src, dst) % 16 == 0 &&
-                      log2n >= b + bz && log2n - b - bz <= 32;
-    if (fits) {
-      a.rect_bz = bz;
-      a.t.m = log2n - b - bz;
-      a.t.items_per_seg = 1ull << a.t.m;
-      a.t.total_items = a.t.items_per_seg * (uint64_t)rows;
-    } else if (cfg && cfg->variant) {
-      return BITREV_ERROR_NOT_SUPPORTED;
-    }
-  }
-  a.t.balanced = order_code((cfg && cfg->order) ? cfg->order : (tp.order ? tp.order : 2));
-  const int xr = (cfg && cfg->xcd_remap) ? cfg->xcd_remap : (tp.xcd ? tp.xcd : 1);
-  a.t.xcds = xr == 2 ? 1 : d.xcds;
-  a.t.grid = (cfg && cfg->grid_blocks > 0) ? round_up((uint64_t)cfg->grid_blocks, (uint32_t)d.xcds)
-                                           : default_grid(a.t.total_items, d);
-  a.t.pipelined = 0;
-  a.t.hints = (cfg && cfg->cache_hints) ? cfg->cache_hints - 1
-                                        : (tp.hints ? tp.hints - 1 : kHintPlain);
-  a.stages = stages;
-  a.inverse = inverse;
-  const size_t vb = (s << b) < 16 ? (s << b) : 16;
-  const bool vec = pointer_align(src, dst) % vb == 0;
-  const hipError_t e = s == 8 ? launch_dit_s8(b, vec, a, static_cast<hipStream_t>(stream))
-                              : launch_dit_s16(b, vec, a, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? BITREV_SUCCESS : hip_fail(e);
 }
 
@@ -1691,6 +1731,40 @@ bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays
   plan->cache_hints = a.hints + 1;
   plan->lds_bytes = p.lds;
   *whole_bits = a.whole;
+  return BITREV_SUCCESS;
+}
+
+bitrev_status_t bitrev_debug_dit_plan(int log2n, int64_t rows, int stages, int outofplace,
+                                      int dtype, size_t align, const bitrev_config_t* cfg,
+                                      bitrev_plan_t* plan) {
+  if (plan == NULL || log2n < 0 || log2n > 40 || rows < 1 || rows > (1ll << (50 - log2n)) ||
+      stages < 1 || 2 * stages > log2n || (dtype != 0 && dtype != 1) ||
+      stages > max_tile_bits(dtype == 0 ? 8 : 16) || !(align == 16 || (align == 8 && dtype == 0)) ||
+      !valid_config(cfg))
+    return BITREV_ERROR_INVALID_VALUE;
+  DeviceInfo d;
+  bitrev_status_t st = device_info(&d, true);
+  if (st != BITREV_SUCCESS) return st;
+  DitPlan p;
+  st = plan_dit(outofplace == 0, log2n, rows, stages, dtype == 0 ? 8 : 16, cfg, align, d, &p);
+  if (st != BITREV_SUCCESS) return st;
+  memset(plan, 0, sizeof *plan);
+  plan->vector_access = p.vec ? 1 : 0;
+  if (p.whole_rows) {
+    plan->path = BITREV_PATH_ROWS;
+    plan->grid_blocks = (int)p.r.grid;
+    plan->cache_hints = p.r.hints + 1;
+    return BITREV_SUCCESS;
+  }
+  plan->path = BITREV_PATH_TILE;
+  plan->tile_bits = p.b;
+  plan->mid_bits = p.a.t.m;
+  plan->grid_blocks = (int)p.a.t.grid;
+  plan->order = p.order;
+  plan->variant = p.a.rs ? 3 : p.a.rect_bz ? 1 + p.b - p.a.rect_bz : 1;
+  plan->xcd_remap = p.xcd_remap;
+  plan->cache_hints = p.a.t.hints + 1;
+  plan->work_items = p.a.t.total_items;
   return BITREV_SUCCESS;
 }
 

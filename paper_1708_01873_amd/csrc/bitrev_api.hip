@@ -412,8 +412,11 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //    four levels 11.2 -> 10.5).  Elsewhere it loses (one level: 2^13 23 MiB
 //    8.2 -> 10.2, 2^16 15 MiB 5.8 -> 7.3, one array of 2^21 12.1 -> 13.8) or
 //    is level from cold caches (2^12 15 MiB, four levels 6.7 -> 6.1, 10.2).
+// `width`: the tile width that the caller or an exact tuning entry sets, if any.
+// The rule's fields were measured together: at another width than its own the
+// table decides.
 PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint, int stages,
-                      bool linear, const DeviceInfo& dev) {
+                      bool linear, int width, const DeviceInfo& dev) {
   PlanFields f;
   if (dev.cus != 256 || !arch_matches("gfx950", dev.arch)) return f;
   auto set = [&f](int b, int variant, int order, int xcd, int hints) {
@@ -457,7 +460,9 @@ PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint,
   } else if (footprint >= 24 * mib && footprint <= 40 * mib && s == 8 && k >= 11 && stages == 6) {
     set(6, 2, 1, rows >= 2 ? 2 : 1, 1);
   }
-  return f.b && user_rows_apply(kind, s, footprint, dev) ? PlanFields() : f;
+  if (!f.b || (width && width != f.b) || user_rows_apply(kind, s, footprint, dev))
+    return PlanFields();
+  return f;
 }
 
 // ---------------------------------------------------------------------------
@@ -640,7 +645,8 @@ bitrev_status_t plan_tiles(int mode, int k, int s, int64_t rows, const bitrev_co
   const int kind = mode == kModeInplace ? kKindInplace : kKindOutofplace;
   const PlanFields tp = table_plan(kind, s, 0, 0, footprint, d,
                                    bytes_rule(kind, s, k, rows_u, footprint, 0,
-                                              contiguous && align == 16, d));
+                                              contiguous && align == 16,
+                                              forced_b ? forced_b : te.tile_bits, d));
   p->order = (cfg && cfg->order) ? cfg->order : (te.order ? te.order : (tp.order ? tp.order : 2));
   p->xcd_remap = (cfg && cfg->xcd_remap) ? cfg->xcd_remap
                                          : (te.xcd_remap ? te.xcd_remap : (tp.xcd ? tp.xcd : 1));
@@ -1189,7 +1195,7 @@ static bitrev_status_t plan_dit(bool inplace, int log2n, int64_t rows, int stage
     return BITREV_SUCCESS;
   }
   const PlanFields rule = bytes_rule(kind, (int)s, log2n, (uint64_t)rows, footprint, stages,
-                                     true, d);
+                                     true, cfg ? cfg->tile_bits : 0, d);
   const PlanFields t1 = table_plan(kind, (int)s, 0, 0, footprint, d, rule);
   int b;
   if (cfg && cfg->tile_bits) {

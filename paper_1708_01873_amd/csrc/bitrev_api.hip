@@ -457,7 +457,7 @@ PlanFields bytes_rule(int kind, int s, int k, uint64_t rows, uint64_t footprint,
         footprint >= 6 * mib)
       set(6, 2, 3, 2, 4);
     if (s == 16 && k >= 12 && large && footprint <= 16 * mib) set(6, 2, 1, 1, 4);
-  } else if (footprint >= 24 * mib && footprint <= 40 * mib && s == 8 && k >= 11 && stages == 6) {
+  } else if (footprint >= 24 * mib && footprint <= 40 * mib && s == 8 && stages == 6) {
     set(6, 2, 1, rows >= 2 ? 2 : 1, 1);
   }
   if (!f.b || (width && width != f.b) || user_rows_apply(kind, s, footprint, dev))

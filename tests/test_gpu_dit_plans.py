@@ -44,3 +44,38 @@ def _check(s, k, rows, stages, inplace, shift=0):
                                     (14, 65), (15, 9), (18, 1)])
 def test_complex128_in_place(k, rows, stages):
     _check(16, k, rows, stages, True)
+
+
+@pytest.mark.parametrize("s,k,rows,stages", [
+    # complex64: five levels from 6 MiB, others from 12, to 18 (one level 16)
+    (8, 12, 191, 5), (8, 12, 193, 5), (8, 12, 383, 2), (8, 12, 385, 2), (8, 12, 576, 4),
+    (8, 12, 577, 4), (8, 12, 512, 1), (8, 12, 513, 1), (8, 16, 25, 3), (8, 21, 1, 5),
+    # rows of 2^11: five levels from 12 MiB on 2^5 x 2^4 tiles
+    (8, 11, 767, 5), (8, 11, 769, 5), (8, 11, 1152, 5), (8, 11, 1153, 5),
+    # six levels at 24 to 40 MiB, plain accesses
+    (8, 12, 767, 6), (8, 12, 769, 6), (8, 12, 1281, 6),
+    # complex128: 12 to 16 MiB
+    (16, 12, 191, 3), (16, 12, 193, 3), (16, 12, 193, 6), (16, 12, 256, 5), (16, 12, 257, 5),
+    (16, 14, 50, 1), (16, 16, 13, 2), (16, 20, 1, 4),
+    # several complex128 rows from 128 MiB
+    (16, 16, 127, 3), (16, 16, 129, 3), (16, 19, 17, 1)])
+def test_out_of_place(s, k, rows, stages):
+    _check(s, k, rows, stages, False)
+
+
+@pytest.mark.parametrize("k,rows,stages", [(12, 193, 5), (12, 400, 2), (14, 100, 4), (11, 800, 5),
+                                           (12, 800, 6)])
+def test_out_of_place_off_the_16_byte_grid(k, rows, stages):
+    """Complex64 from an odd element: the rule's square tiles, by elements."""
+    n = 1 << k
+    rng = np.random.default_rng(k * rows)
+    x = (rng.standard_normal((rows, n)) + 1j * rng.standard_normal((rows, n))).astype(np.complex64)
+    src, dst = (torch.zeros(1 + x.size, dtype=torch.complex64, device="cuda")[1:] for _ in "sd")
+    src.copy_(torch.from_numpy(x).reshape(-1))
+    br.bitrev_dit_stages(src.view(rows, n), dst.view(rows, n), stages=stages)
+    got = to_host_bytes(dst).view(np.complex64).reshape(rows, n)
+    u = 2.0 ** -24
+    for r in (0, rows // 2, rows - 1):
+        w = dit.dit_stages(x[r], stages, False, precision=np.complex128).reshape(-1, 1 << stages)
+        err = np.linalg.norm(got[r].astype(np.complex128).reshape(w.shape) - w, axis=1)
+        assert np.all(err <= dit.higham_bound(stages, u, u) * np.linalg.norm(w, axis=1) + 1e-30)

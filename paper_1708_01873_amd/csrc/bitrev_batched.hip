@@ -181,7 +181,7 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
           u32x4 a[CE], r[CE];
 #pragma unroll
           for (int e = 0; e < CE; ++e)
-            a[e] = ld_hint<H>(reinterpret_cast<const u32x4_a4*>(in + q * 16u + ((uint32_t)e << (w + 4))));
+            a[e] = ld_vec<H>(in + q * 16u + ((uint32_t)e << (w + 4)));
           rows_transpose<S>(a, r);
           const uint32_t o = rev_bits(q, w);
 #pragma unroll
@@ -192,8 +192,7 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
 #pragma unroll
       for (int i = 0; i < VPT; ++i) {
         const uint32_t v = t + i * NT;
-        if (v < (1u << lv))
-          st_hint<H>(reinterpret_cast<u32x4_a4*>(out + v * 16u), (u32x4_a4)lds[rows_slot(v)]);
+        if (v < (1u << lv)) st_vec<H>(out + v * 16u, lds[rows_slot(v)]);
       }
       return;
     }
@@ -221,8 +220,7 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
 #pragma unroll
       for (int i = 0; i < VPT; ++i) {
         const uint32_t v = t + i * NT;
-        if (v < (1u << lv))
-          st_hint<H>(reinterpret_cast<u32x4_a4*>(out + v * 16u), (u32x4_a4)lds[rows_slot(v)]);
+        if (v < (1u << lv)) st_vec<H>(out + v * 16u, lds[rows_slot(v)]);
       }
       return;
     }
@@ -233,7 +231,7 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
       const uint32_t v = t + i * NT;
-      if (v < n / CE) lds[v] = *reinterpret_cast<const u32x4_a4*>(in + v * 16u);
+      if (v < n / CE) lds[v] = ld_vec<kHintPlain>(in + v * 16u);
     }
     sync();
 #pragma unroll 1
@@ -241,7 +239,7 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
       Chunk<S, 16> c;
 #pragma unroll
       for (int e = 0; e < CE; ++e) c.e[e] = le[rev_bits(v * CE + e, k)];
-      *reinterpret_cast<u32x4_a4*>(out + v * 16u) = c.v;
+      st_vec<kHintPlain>(out + v * 16u, c.v);
     }
     return;
   }

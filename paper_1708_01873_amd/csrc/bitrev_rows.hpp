@@ -20,8 +20,36 @@
 namespace bitrev {
 
 // 16 bytes at any multiple of 4 bytes: gfx950's wide global accesses need
-// dword alignment only, so rows at a padded pitch move as vectors too.
+// dword alignment only, so rows at a padded pitch move as vectors too.  The
+// accessors name the type: a template parameter deduced from it would be the
+// vector without the attribute, and the access would claim 16.
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+template <int H> __device__ __forceinline__ u32x4 ld_vec(const u32x4_a4* q) {
+  if constexpr (H == kHintStreamLoads || H == kHintStreamWriteThrough) {
+    return __builtin_nontemporal_load(q);
+  } else {
+    return *q;
+  }
+}
+
+template <int H> __device__ __forceinline__ u32x4 ld_vec(const char* p) {
+  return ld_vec<H>(reinterpret_cast<const u32x4_a4*>(p));
+}
+
+template <int H> __device__ __forceinline__ void st_vec(u32x4_a4* q, u32x4 v) {
+  if constexpr (H == kHintStreamStores) {
+    __builtin_nontemporal_store(v, q);
+  } else if constexpr (H == kHintStreamWriteThrough) {
+    st_through(reinterpret_cast<u32x4*>(q), v);  // one instruction: it claims nothing
+  } else {
+    *q = v;
+  }
+}
+
+template <int H> __device__ __forceinline__ void st_vec(char* p, u32x4 v) {
+  st_vec<H>(reinterpret_cast<u32x4_a4*>(p), v);
+}
 
 // log2 of the elements per 16-byte vector.
 __host__ __device__ constexpr int vec_log2(int s) { return s == 16 ? 0 : s == 8 ? 1 : s == 4 ? 2 : s == 2 ? 3 : 4; }
@@ -108,7 +136,7 @@ __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, v
         const char* p = in + r * src_pitch + q * 16u;
 #pragma unroll
         for (int e = 0; e < CE; ++e)
-          a[e] = ld_hint<LH>(reinterpret_cast<const u32x4_a4*>(p + ((size_t)e << (w + 4))));
+          a[e] = ld_vec<LH>(p + ((size_t)e << (w + 4)));
         rows_transpose<S>(a, t);
         const uint32_t o = (r << lv) + rev_bits(q, w);
 #pragma unroll
@@ -121,8 +149,7 @@ __global__ __launch_bounds__(rows_threads(S, LB)) void k_rows(const void* src, v
       const uint32_t v = threadIdx.x + i * NT;
       const uint32_t r = v >> lv;
       if (r < live)
-        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + r * dst_pitch + (v & vmask) * 16u),
-                   (u32x4_a4)lds[rows_slot(v)]);
+        st_vec<H>(out + r * dst_pitch + (v & vmask) * 16u, lds[rows_slot(v)]);
     }
     __syncthreads();
   }
@@ -192,8 +219,7 @@ __global__ __launch_bounds__(bytes_threads(LB)) void k_rows_bytes(const void* sr
       const uint32_t v = threadIdx.x + i * NT;
       const uint32_t s = v >> lv;
       if (s < live)
-        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + s * dst_pitch + (v & vmask) * 16u),
-                   (u32x4_a4)lds[rows_slot(v)]);
+        st_vec<H>(out + s * dst_pitch + (v & vmask) * 16u, lds[rows_slot(v)]);
     }
     __syncthreads();
   }
@@ -224,8 +250,7 @@ __global__ __launch_bounds__(gather_threads(LB)) void k_rows_gather(
       const uint32_t v = threadIdx.x + i * NT;
       const uint32_t r = v >> lr;
       if (r < live)
-        lds[v] = ld_hint<H>(
-            reinterpret_cast<const u32x4_a4*>(in + r * src_pitch + (v & rmask) * 16u));
+        lds[v] = ld_vec<H>(in + r * src_pitch + (v & rmask) * 16u);
     }
     __syncthreads();
 #pragma unroll 1
@@ -239,8 +264,7 @@ __global__ __launch_bounds__(gather_threads(LB)) void k_rows_gather(
           const uint32_t o = v * CE + e;
           c.e[e] = le[(o & ~nmask) | rev_bits(o & nmask, k)];
         }
-        st_hint<H>(reinterpret_cast<u32x4_a4*>(out + r * dst_pitch + (v & rmask) * 16u),
-                   (u32x4_a4)c.v);
+        st_vec<H>(out + r * dst_pitch + (v & rmask) * 16u, c.v);
       }
     }
     __syncthreads();
@@ -290,7 +314,7 @@ __global__ __launch_bounds__(dit_rows_threads(LB)) void k_rows_dit(const void* s
     if (r < live) {
       Chunk<S, 16> a[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e].v = ld_hint<LH>(in + (r << lv) + q + ((uint32_t)e << w));
+      for (int e = 0; e < 8; ++e) a[e].v = ld_vec<LH>(in + (r << lv) + q + ((uint32_t)e << w));
 #pragma unroll
       for (int j = 0; j < CE; ++j) {
         F re[8], im[8];
@@ -319,7 +343,7 @@ __global__ __launch_bounds__(dit_rows_threads(LB)) void k_rows_dit(const void* s
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const uint32_t v = threadIdx.x + i * NT;
-      if ((v >> lv) < live) st_hint<H>(out + v, (u32x4_a4)lds[rows_slot(v)]);
+      if ((v >> lv) < live) st_vec<H>(out + v, lds[rows_slot(v)]);
     }
     __syncthreads();
   }

@@ -38,7 +38,8 @@ template <int S, int H, int LH> hipError_t run_rows_s(const RowsLaunch& a, hipSt
     if constexpr (S == 16)
       if (a.chunk_log2 == 13) return run_rows<S, 13, H, LH>(a, st);
     if (a.chunk_log2 == 14) return run_rows<S, 14, H, LH>(a, st);
-    if constexpr (H == kHintPlain) {
+    // (16-byte elements are always on the 16-byte grid: rows of 16 KiB at most)
+    if constexpr (H == kHintPlain && S < 16) {
       if (a.chunk_log2 == 15) return run_rows<S, 15, H, LH>(a, st);
       if (a.chunk_log2 == 16) return run_rows<S, 16, H, LH>(a, st);
     }

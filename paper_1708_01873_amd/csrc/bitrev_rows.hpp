@@ -60,7 +60,7 @@ __host__ __device__ constexpr int vec_log2(int s) { return s == 16 ? 0 : s == 8 
 // 1024 threads, and at 16 bytes 8 KiB chunks of one were 2% ahead of 16 KiB
 // of two at 128-512 MiB.
 __host__ __device__ constexpr int rows_groups(int s, int lb) {
-  return s == 16 ? (lb >= 16 ? 4 : lb >= 14 ? 2 : 1) : (s == 8 && lb >= 15) ? 2 : 1;
+  return (s == 16 && lb >= 14) || (s == 8 && lb >= 15) ? 2 : 1;
 }
 
 // Threads of a workgroup of k_rows whose chunk has 2^lb bytes.

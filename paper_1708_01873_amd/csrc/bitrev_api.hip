@@ -770,8 +770,8 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   int b = (cfg && cfg->tile_bits) ? cfg->tile_bits
                                   : (te.tile_bits ? te.tile_bits : (t1.b ? t1.b : max_tile_bits(s)));
   if (!(cfg && cfg->tile_bits) && b > max_tile_bits(s)) b = max_tile_bits(s);
-  if (b < kMinBatchedTileBits || b > max_tile_bits(s) ||
-      tile_lds_bytes_for(s, b, 2) > d.lds_per_block)
+  p->lds = tile_lds_bytes_for(s, b, oop ? 1 : 2);
+  if (b < kMinBatchedTileBits || b > max_tile_bits(s) || p->lds > d.lds_per_block)
     return BITREV_ERROR_NOT_SUPPORTED;
   p->path = BITREV_PATH_BATCHED;
   p->b = b;
@@ -786,7 +786,6 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   p->persistent = (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || file.wg > 0;
   p->forced_xcd = (cfg && cfg->xcd_remap) || te.xcd_remap || file.xcd;
   p->threads = threads_of(s, b, true);
-  p->lds = tile_lds_bytes_for(s, b, 2);
   int per_cu = te.wg_per_cu > 0 ? te.wg_per_cu : tp.wg;
   if (per_cu <= 0) {
     // resident at once: LDS and threads, and the registers the kernel needs
@@ -1063,10 +1062,11 @@ bitrev_status_t run_digit(const void* src, void* dst, int k, int d, size_t s,
   const int kind = inplace ? kKindDigitInplace : kKindDigitOutofplace;
   const PlanFields t1 = table_plan(kind, (int)s, d, 0, n * s, dev);
   int b = t1.b ? t1.b : max_tile_bits((int)s);
+  const int tiles = inplace ? 2 : 1;  // staged by a workgroup
   if (cfg && cfg->tile_bits) {
     b = cfg->tile_bits;  // forced: whole digits, within the array, compiled, fits
     if (b % d || 2 * b > k || b > max_tile_bits((int)s) ||
-        tile_lds_bytes_for((int)s, b, 2) > dev.lds_per_block)
+        tile_lds_bytes_for((int)s, b, tiles) > dev.lds_per_block)
       return BITREV_ERROR_NOT_SUPPORTED;
   } else {
     // b must be a multiple of d: round up where the element size and the
@@ -1076,7 +1076,7 @@ bitrev_status_t run_digit(const void* src, void* dst, int k, int d, size_t s,
     if (b > max_tile_bits((int)s)) b = max_tile_bits((int)s);
     if (2 * b > k) b = k / 2;
     b -= b % d;
-    while (b >= d && tile_lds_bytes_for((int)s, b, 2) > dev.lds_per_block) b -= d;
+    while (b >= d && tile_lds_bytes_for((int)s, b, tiles) > dev.lds_per_block) b -= d;
   }
   if (b < d) return BITREV_ERROR_NOT_SUPPORTED;
   const int m = k - 2 * b;

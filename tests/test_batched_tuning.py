@@ -119,3 +119,20 @@ def test_a_mapping_is_honoured_from_every_source(tuned, elems, num, s, xcd):
         assert launch(elems, num, s) == want, (b, wg)
         tuned("* 0 batched %d 0 0 -1 -1   %d %d 2 0 %d 0" % (s, b, wg, xcd))
         assert launch(elems, num, s) == want, (b, wg)
+
+
+@pytest.mark.parametrize("s", (1, 2, 4, 8, 16))
+def test_out_of_place_stages_one_tile(s):
+    """Tiles staged by a workgroup of the tile kernel: a pair in place, one out
+    of place, whatever the width; what residency and limits are computed from."""
+    config, whole = br.Config(), ctypes.c_int()
+    for b in range(4, {1: 7, 2: 7, 4: 7, 8: 6, 16: 6}[s] + 1):
+        config.tile_bits = b
+        lds = []
+        for oop in (0, 1):
+            p = br.Plan()
+            assert br.lib().bitrev_debug_batched_plan(
+                1 << 20, 3, s, oop, ctypes.byref(config), ctypes.byref(p),
+                ctypes.byref(whole)) == br.SUCCESS
+            lds.append(p.lds_bytes)
+        assert lds[0] == 2 * lds[1] and lds[1] >= s << (2 * b)

@@ -36,12 +36,18 @@ def _permute(x: torch.Tensor) -> torch.Tensor:
     return y
 
 
+def _unknown() -> bool:
+    return True
+
+
 def _recorded() -> bool:
     """Whether grad mode, a functorch transform, a forward-mode level or a
-    trace sees what is computed now."""
-    return (torch.is_grad_enabled() or torch._C._are_functorch_transforms_active()
+    trace sees what is computed now.  Torch has no public names for the last
+    three: a build without one of these counts as recording."""
+    return (torch.is_grad_enabled()
+            or getattr(torch._C, "_are_functorch_transforms_active", _unknown)()
             or getattr(torch.autograd.forward_ad, "_current_level", 0) >= 0
-            or torch._C._get_tracing_state() is not None)
+            or getattr(torch._C, "_get_tracing_state", _unknown)() is not None)
 
 
 class BitRev(torch.autograd.Function):

@@ -93,10 +93,14 @@ typedef struct bitrev_config {
                     * XCD's L2 to the memory side instead of staying dirty
                     * there); applies to the one-item and register-staged
                     * tile kernels with 16-byte accesses, otherwise plain.
-                    * The choice: plain below 32 MiB out of place and 64 MiB
-                    * in place; streaming loads for 1- and 2-byte elements
-                    * beyond 256 MiB and for 4-byte elements out of place
-                    * at 128-256 MiB; 4 otherwise */
+                    * The choice: 4 from 32 MiB out of place and 64 MiB in
+                    * place, but streaming loads for 1- and 2-byte elements
+                    * from 512 MiB and for 4-byte elements out of place at
+                    * 256-512 MiB; plain below, but 4 where the plan takes
+                    * narrow one-item tiles (2-byte elements to 16 MiB in
+                    * place and at 4-16 MiB out of place, 4-byte at 8-16 and
+                    * 32-64 MiB in place, 16-byte at 4-64 MiB in place and
+                    * 8-16 MiB out of place) */
 } bitrev_config_t;
 
 /* Which code path and geometry a call uses (bitrev_plan_query). */
@@ -171,7 +175,7 @@ bitrev_status_t bitrev_evenodd(const void* src, void* dst, int log2n, int64_t ro
                                size_t elem_size, void* stream);
 
 /* ------------------------------------------------------------------------ */
-/* Batched: many arrays of different lengths in one persistent launch        */
+/* Batched: many arrays of different lengths in two launches                 */
 /* ------------------------------------------------------------------------ */
 
 /* Bytes of device workspace bitrev_batched needs for num_arrays arrays
@@ -191,9 +195,9 @@ size_t bitrev_batched_workspace_size(int64_t num_arrays);
  *              bitrev_batched_errors()
  * Two kernels are enqueued: one whose first workgroups check every
  * array (offsets[a+1] - offsets[a] == 2^log2n[a], 0 <= offsets[a],
- * offsets[a+1] <= data_elems, 0 <= log2n[a] <= BITREV_MAX_LOG2N) and scans
- * the per-array work counts into the workspace, and whose others move the
- * short arrays, then the kernel for the tiles of the long ones.
+ * offsets[a+1] <= data_elems, 0 <= log2n[a] <= BITREV_MAX_LOG2N) and scan the
+ * per-array work counts into the workspace, and whose others move the short
+ * arrays, then the kernel for the tiles of the long ones.
  * A rejected array is left untouched; the others are still permuted.
  * Arrays must not overlap (the length check makes valid ones disjoint). */
 bitrev_status_t bitrev_batched(void* data, int64_t data_elems, const int64_t* offsets,

@@ -119,7 +119,7 @@ bool valid_elem_size(size_t s) { return s == 1 || s == 2 || s == 4 || s == 8 || 
 
 // ---------------------------------------------------------------------------
 // Plan table: the tile width, kernel variant, work order, XCD mapping, cache
-// hints and persistent workgroups per CU of each kind of launch, by device
+// hints and workgroups per CU of each kind of launch, by device
 // (gcnArchName and compute units), element size, digit width, tile width in
 // use and footprint class.  The built-in rows are data (plans_gfx950.inc,
 // regenerated by the autotuner); rows of the same form in a tuning file are
@@ -375,7 +375,7 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
 //  - Several rows, in dispatch order, which walks the rows one after the
 //    other where contiguous XCD ranges keep eight distant rows in flight:
 //    complex128 rows of 1 to 8 MiB from 64 MiB on (68 MiB of 2^17 22.8 ->
-//    21.8, 124 MiB 46.2 -> 41.4, 204 MiB of 2^18 67.4 -> 67.5), float32
+//    21.8, 124 MiB 46.2 -> 41.4; level at 204 MiB of 2^18, 67.5), float32
 //    rows of 256 KiB to 4 MiB from 256 MiB on at b = 7 (330 MiB of 2^17 128.6
 //    -> 117.2, 488 MiB of 2^16 179.4 -> 172.7), fused levels up to five on
 //    complex128 rows of 1 to 8 MiB from 128 MiB on (152 MiB of 2^17 57.0 ->
@@ -1658,7 +1658,7 @@ bitrev_status_t bitrev_batched_noalloc(void* data, int64_t data_elems, const int
   void* ws = nullptr;
   const bitrev_status_t st = scratch_address(&ws);
   if (st != BITREV_SUCCESS) return st;
-  // the first kernel writes every workspace word the persistent kernel reads
+  // the first kernel writes every workspace word the second one reads
   // (header and scan), so the previous call's contents need no clearing
   return run_batched(NULL, data, data_elems, offsets, log2n, num_arrays, elem_size, ws,
                      sizeof(scratch), NULL, stream);

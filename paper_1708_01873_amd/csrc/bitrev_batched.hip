@@ -278,11 +278,13 @@ __device__ __forceinline__ void whole_array(const char* in, char* out, int k, u3
 // arrays beyond 4 KiB take the whole workgroup, one after the other, and the
 // others one wavefront each, in turn.
 //
-// Bound by latency: an array is one chain of metadata, load and store, and 7
-// wavefronts per SIMD of such chains are in flight.  Measured on 20000 uneven
-// complex64 arrays of 2^0-2^12 out of place (a copy of the bytes: 31 us), the
-// two kernels of a call together: 188 us where the persistent kernel took
-// each array with 1024 threads, after a search for it in the scan; 51 us.
+// Bound by latency: an array is one chain of metadata, load and store, and
+// those beyond 4 KiB follow one another in their workgroup; the 95 registers
+// of the 8-byte kernel leave two workgroups of 32 KiB per CU, four wavefronts
+// per SIMD.  Measured on 20000 uneven complex64 arrays of 2^0-2^12 out of place
+// (a copy of the bytes: 31 us), the two kernels of a call together: 188 us
+// where a persistent kernel took each array with 1024 threads, after a search
+// for it in the scan; 51 us.
 template <int S, int LB, int H>
 __global__ __launch_bounds__(front_threads(LB)) void k_batched_front(const void* src, void* data,
                                                                  BatchMeta m, int scan_blocks,

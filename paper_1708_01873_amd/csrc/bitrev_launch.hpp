@@ -56,7 +56,7 @@ struct RowsLaunch {
   uint64_t src_pitch;       // bytes between consecutive runs
   uint64_t dst_pitch;
   int chunk_log2;           // bytes per workgroup
-  bool gather;              // element by element (k < 2 log2(16 / s), and bytes)
+  bool gather;              // element by element (k < 2 log2(16 / s))
   int hints;                // plain or streaming loads with write-through stores
   uint32_t grid;
 };
@@ -67,8 +67,8 @@ struct DitLaunch {
   int inverse;              // 1: exp(+2 pi i ...) twiddles
   int rect_bz = 0;          // > 0: out of place with rectangular tiles of
                             // 2^b source rows of 2^rect_bz elements
-  int rs = 0;               // 1: in place, complex64, the pair held in
-                            // registers and staged through one LDS tile
+  int rs = 0;               // 1: in place, the pair held in registers and
+                            // staged through one LDS tile
 };
 
 struct TransposeLaunch {

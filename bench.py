@@ -500,7 +500,7 @@ def traffic_workload(torch, br, workloads) -> None:
     l2 = torch.from_numpy(log2n).cuda()
     ws = torch.empty(br.bitrev_batched_workspace_size(len(log2n)), dtype=torch.uint8,
                      device="cuda")
-    run("batched 4096 complex64 arrays, log2n in [8, 20] (prep + main kernel)",
+    run("batched 4096 complex64 arrays, log2n in [8, 20] (two kernels)",
         lambda: br.bitrev_batched(data, off, l2, ws), 2, 2, 2 * int(offsets[-1]) * 8)
 
 

@@ -739,10 +739,11 @@ __device__ __forceinline__ int64_t find_array(const int64_t* scan, int64_t num, 
   return lo;
 }
 
-// Batched, in place, persistent: k_batched_front has permuted the arrays that
-// fit its LDS and written the exclusive scan of the tile pairs of the others
-// to ws[2..]; every workgroup walks the global work ids with a grid stride,
-// finds its array and swaps one tile pair at width b.
+// Batched, in place: k_batched_front has permuted the arrays that fit its LDS
+// and written the exclusive scan of the tile pairs of the others to ws[2..]; a
+// workgroup finds the array of its work id and swaps one tile pair at width b.
+// The library's own grid has a workgroup for each id up to 256 per CU; a grid
+// that the caller or a tuning file counts out walks the ids with its stride.
 template <int S, int B>
 __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched(
     void* data, const int64_t* offsets, const int32_t* log2n, int64_t num, const int64_t* ws,
@@ -772,8 +773,8 @@ __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched(
   }
 }
 
-// Batched, out of place: the same persistent walk, with one work item per
-// source tile (2^m per array); dst holds the same layout.
+// Batched, out of place: the same, with one work item per source tile (2^m per
+// array); dst holds the same layout.
 template <int S, int B>
 __global__ __launch_bounds__((tile_threads<S, B, true>())) void k_batched_oop(
     const void* src, void* dst, const int64_t* offsets, const int32_t* log2n, int64_t num,

@@ -210,11 +210,13 @@ int parse_plan_row(const char* line, PlanRow* r) {
   return 0;
 }
 
-std::vector<PlanRow> g_builtin_rows;
+std::vector<PlanRow> g_builtin_rows[kKindCount];
 std::vector<PlanRow> g_user_rows;  // guarded by g_tune_mu
 std::once_flag g_builtin_once;
 
-const std::vector<PlanRow>& builtin_rows() {
+// The built-in rows of one kind: a call looks at these and its parents' only
+// (the whole table in every call cost 0.1 us of a small array's 3.6).
+const std::vector<PlanRow>& builtin_rows(int kind) {
   std::call_once(g_builtin_once, [] {
     const char* p = kBuiltinPlans;
     char line[512];
@@ -226,11 +228,11 @@ const std::vector<PlanRow>& builtin_rows() {
       char* hash = strchr(line, '#');
       if (hash) *hash = '\0';
       PlanRow r;
-      if (parse_plan_row(line, &r) == 0) g_builtin_rows.push_back(r);
+      if (parse_plan_row(line, &r) == 0) g_builtin_rows[r.kind].push_back(r);
       p += n + (p[n] == '\n');
     }
   });
-  return g_builtin_rows;
+  return g_builtin_rows[kind];
 }
 
 bool arch_matches(const char* row, const char* dev) {
@@ -353,7 +355,6 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
                       PlanFields f = PlanFields(), PlanFields* file = nullptr) {
   load_env_tuning();
   const int c = footprint_class(footprint);
-  const std::vector<PlanRow>& builtin = builtin_rows();
   std::lock_guard<std::mutex> lock(g_tune_mu);
   for (int k = kind; k >= 0; k = kKindParent[k]) {
     const PlanFields before = f;
@@ -363,7 +364,7 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
       if (!before.wg) file->wg = f.wg;
       if (!before.xcd) file->xcd = f.xcd;
     }
-    merge_rows(builtin, k, s, d, bm, c, dev, &f);
+    merge_rows(builtin_rows(k), k, s, d, bm, c, dev, &f);
   }
   return f;
 }
@@ -562,8 +563,8 @@ struct Plan {
 
 // The whole-row path (bitrev_rows.hpp) for `rows` >= 2 arrays of 2^k elements
 // whose accesses stay 4-byte aligned: true and *p filled where it is taken,
-// given the tile plan *p.  The lines, each with both sides measured (kernel
-// time, three matrices in turn):
+// unless the tile plan is one linear tile per row (which plan_plain asks).  The
+// lines, each with both sides measured (kernel time, three matrices in turn):
 //  - rows of at most 16 KiB, from 8 KiB on only bytes or 64 MiB (complex64
 //    2^11 128 MiB 43.1 -> 41.4, 36 MiB 12.2 against 12.6; rows of 32 KiB lose
 //    1-8%); off the 16-byte grid, where the tile kernels move single elements,
@@ -591,9 +592,6 @@ bool plan_rows(int k, int s, uint64_t rows, size_t align, bool contiguous, bool 
   if (rows < 2 || k > 16 || align < 4 || (rb < 16 && !contiguous)) return false;
   const bool aligned = align == 16;
   if (rb > 65536u) return false;
-  const bool linear_tile = p->path == BITREV_PATH_TILE && p->m == 0 && p->vec && p->b >= 4;
-  if (linear_tile && (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20)))))
-    return false;
   if (aligned && rb >= 8192 && (rb > 16384 || (s > 1 && footprint < (64ull << 20)))) return false;
   const bool gather = k < 2 * c;
   if (gather && footprint < ((rb >= 16 ? 512u : 32u) << 10)) return false;
@@ -718,26 +716,30 @@ bitrev_status_t plan_plain(int mode, int k, int s, int64_t rows, uint64_t src_pi
   const auto tiles = [&] {
     return plan_tiles(mode, k, s, rows, cfg, align, contiguous, d, have_device, p);
   };
-  if (rows < 2 || k > 16 || (mode == kModeInplace && k <= 1) || config_set(cfg)) return tiles();
-  const TuneEntry te = tune_lookup(mode, s, k);
+  if (rows < 2 || k > 16 || (mode == kModeInplace && k <= 1) || config_set(cfg) ||
+      (uint64_t)rows > (1ull << 62) >> k)
+    return tiles();
+  // arithmetic before the tuning tables' locks and lookups, which a call that
+  // stays with the tiles makes once more
   const uint64_t footprint = (n * (uint64_t)s) * (uint64_t)rows;
+  const bool whole_lines = contiguous || ((src_pitch * s) % 64 == 0 && (dst_pitch * s) % 64 == 0);
+  Plan whole;
+  if (!plan_rows(k, s, (uint64_t)rows, align, contiguous, whole_lines, footprint, &whole))
+    return tiles();
+  // the tile plan is made only where it may be one linear tile per row
+  const uint64_t rb = n * (uint64_t)s;
+  if (align == 16 && k >= 8 && k % 2 == 0 &&
+      (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20))))) {
+    const bitrev_status_t st = tiles();
+    if (st != BITREV_SUCCESS || (p->path == BITREV_PATH_TILE && p->m == 0 && p->vec && p->b >= 4))
+      return st;
+  }
+  const TuneEntry te = tune_lookup(mode, s, k);
   if (te.tile_bits || te.wg_per_cu || te.order || te.variant || te.xcd_remap || te.cache_hints ||
-      (uint64_t)rows > (1ull << 62) >> k ||
       user_rows_apply(mode == kModeInplace ? kKindInplace : kKindOutofplace, s, footprint, d))
     return tiles();
-  const bool whole_lines = contiguous || ((src_pitch * s) % 64 == 0 && (dst_pitch * s) % 64 == 0);
-  // the tile plan is made first only where it may be one linear tile per row
-  *p = Plan();
-  const uint64_t rb = n * (uint64_t)s;
-  const bool ask_tiles = align == 16 && k >= 8 && k % 2 == 0 &&
-                         (rb >= 2048 || (rb == 1024 && (s == 1 || footprint >= (64ull << 20))));
-  if (ask_tiles) {
-    const bitrev_status_t st = tiles();
-    if (st != BITREV_SUCCESS) return st;
-  }
-  if (plan_rows(k, s, (uint64_t)rows, align, contiguous, whole_lines, footprint, p) || ask_tiles)
-    return BITREV_SUCCESS;
-  return tiles();
+  *p = whole;
+  return BITREV_SUCCESS;
 }
 
 // Workgroups of the batched kernel that fit on one CU at once: limited by

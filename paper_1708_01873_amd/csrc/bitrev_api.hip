@@ -350,7 +350,8 @@ TuneEntry tune_lookup(int mode, int s, int k) {
 // The table's plan for a launch of `kind` covering `footprint` bytes; bm is
 // the tile width in use (0 while it is being chosen), d the digit width.
 // Fields no row sets stay 0.  `f` starts with what is already decided; *file,
-// where given, gets the width, count and XCD mapping that a tuning file's rows set.
+// where given, gets the width, count, order and XCD mapping that a tuning file's
+// rows set.
 PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const DeviceInfo& dev,
                       PlanFields f = PlanFields(), PlanFields* file = nullptr) {
   load_env_tuning();
@@ -363,6 +364,7 @@ PlanFields table_plan(int kind, int s, int d, int bm, uint64_t footprint, const 
       if (!before.b) file->b = f.b;
       if (!before.wg) file->wg = f.wg;
       if (!before.xcd) file->xcd = f.xcd;
+      if (!before.order) file->order = f.order;
     }
     merge_rows(builtin_rows(k), k, s, d, bm, c, dev, &f);
   }
@@ -557,6 +559,7 @@ struct Plan {
   bool persistent = false; // batched: the caller or a tuning file set the grid
   bool forced_width = false;  // batched: ... set the tile width
   bool forced_xcd = false;    // batched: ... set the XCD mapping
+  bool forced_order = false;  // batched: ... set the order
   int chunk_log2 = 0;      // whole-row path: bytes per workgroup
   bool gather = false;
 };
@@ -787,6 +790,7 @@ bitrev_status_t plan_batched(int s, const bitrev_config_t* cfg, const DeviceInfo
   // tile per workgroup, which the tuner timed such a row with)
   p->persistent = (cfg && cfg->grid_blocks > 0) || te.wg_per_cu > 0 || file.wg > 0;
   p->forced_xcd = (cfg && cfg->xcd_remap) || te.xcd_remap || file.xcd;
+  p->forced_order = (cfg && cfg->order) || te.order || file.order;
   p->threads = threads_of(s, b, true);
   int per_cu = te.wg_per_cu > 0 ? te.wg_per_cu : tp.wg;
   if (per_cu <= 0) {
@@ -1510,8 +1514,8 @@ static bitrev_status_t check_batched_args(const void* src, void* data, int64_t d
   return BITREV_SUCCESS;
 }
 
-// What a batched launch takes from the plan and from the batch: a->num and
-// a->data_elems are set, the geometry is filled in.
+// What a batched launch takes from the plan and from the batch: a->src, a->num
+// and a->data_elems are set, the geometry is filled in.
 static void batched_geometry(const Plan& p, size_t elem_size, const DeviceInfo& d,
                              BatchedLaunch* a) {
   a->b = p.b;
@@ -1527,7 +1531,16 @@ static void batched_geometry(const Plan& p, size_t elem_size, const DeviceInfo& 
     while ((elem_size << (a->whole + 1)) <= (shorts ? 32768u : 16384u)) ++a->whole;
   a->hints =
       (uint64_t)a->data_elems >= (64ull << 20) / elem_size ? kHintStreamWriteThrough : kHintPlain;
-  a->balanced = order_code(p.order);
+  // Long complex128 arrays in place in the grouped order (8 arrays of 32 MiB
+  // 107.5 -> 97.1 us, from cold caches 101.1 -> 84.0, where one item per
+  // workgroup in the balanced order had lost to the persistent grid's 92.9; 2 of
+  // 256 MiB 231 -> 221 and 184 -> 178; 64 of 2^0-2^20 52.6 -> 50.4; one of 256
+  // MiB 118 -> 109, but 87 -> 94).  Below 1 MiB on average it is level or loses
+  // 1 to 3% (5000 of 2^3-2^13 51.6 -> 52.7, 700 of 2^10-2^16 70.7 -> 71.3).
+  const bool grouped = elem_size == 16 && !p.forced_order && a->src == nullptr &&
+                       (uint64_t)a->data_elems / (uint64_t)a->num >= (1ull << 20) / 16;
+  a->order = grouped ? 3 : p.order;
+  a->balanced = order_code(a->order);
   // one item per workgroup runs in dispatch order unless the caller or a tuning
   // file asks otherwise: contiguous XCD ranges walk eight distant regions at
   // once (4096 complex64 arrays: +10%)
@@ -1725,6 +1738,7 @@ bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays
   st = plan_batched((int)elem_size, cfg, d, have_device, outofplace != 0, &p);
   if (st != BITREV_SUCCESS) return st;
   BatchedLaunch a = {};
+  a.src = outofplace ? plan : nullptr;  // (only whether there is one counts)
   a.num = num_arrays;
   a.data_elems = data_elems;
   batched_geometry(p, elem_size, d, &a);
@@ -1733,7 +1747,7 @@ bitrev_status_t bitrev_debug_batched_plan(int64_t data_elems, int64_t num_arrays
   plan->tile_bits = a.b;
   plan->block_threads = p.threads;
   plan->grid_blocks = (int)a.grid;
-  plan->order = p.order;
+  plan->order = a.order;
   plan->vector_access = 1;
   plan->xcd_remap = a.xcds > 1 ? 1 : 2;
   plan->cache_hints = a.hints + 1;

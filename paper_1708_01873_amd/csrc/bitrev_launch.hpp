@@ -90,6 +90,7 @@ struct BatchedLaunch {
   int b;
   int whole;                // arrays of at most 2^whole elements move whole
   int hints;                // CacheHint of those
+  int order;                // 1 natural, 2 balanced, 3 grouped; `balanced` is its code
   int balanced;
   int xcds;
   uint32_t grid;

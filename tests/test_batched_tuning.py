@@ -136,3 +136,20 @@ def test_out_of_place_stages_one_tile(s):
                 ctypes.byref(whole)) == br.SUCCESS
             lds.append(p.lds_bytes)
         assert lds[0] == 2 * lds[1] and lds[1] >= s << (2 * b)
+
+
+def test_long_complex128_arrays_take_the_grouped_order(tuned):
+    """In place, 1 MiB and more on average, unless somebody sets an order."""
+    def order(elems, num, s=16, **kw):
+        return launch(elems, num, s, **kw)["order"]
+    assert order(8 << 21, 8) == order(1 << 16, 1) == order(100 << 16, 100) == 3
+    assert order((100 << 16) - 1, 100) == order(5000 << 9, 5000) == 2
+    assert order(8 << 21, 8, oop=True) == 2
+    assert order(8 << 21, 8, s=8) == 1
+    assert order(8 << 21, 8, order=1) == 1
+    tuned("* 0 batched 16 0 0 -1 -1   0 0 2 0 0 0")
+    assert order(8 << 21, 8) == 2
+    tuned("batched 16 -1 0 0 1 0 0")
+    assert order(8 << 21, 8) == 1
+    tuned("* 0 batched 16 0 0 -1 -1   0 2 0 0 0 0")
+    assert order(8 << 21, 8) == 3
